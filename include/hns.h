@@ -438,6 +438,19 @@ int hns_operator_assembly(const hns_operator *op);
  *                  takes at most 4 MiB (524288 FP64 / 1048576 FP32 rows),
  *                  0 never, 1 always.  Per-kernel timing then times the
  *                  product (with the direction update) and the update.
+ *   "one_launch"   the Jacobi-scaled recurrence above in one cooperative launch
+ *                  per chunk of up to max(check_every, 1024) iterations, the
+ *                  vectors on chip and the workgroups meeting once per dot
+ *                  product: the same recurrence and stopping rule, the dot
+ *                  products summed in another order.  -1 (default) where a
+ *                  tiling fits (7 upper diagonals; the rows of one tile's
+ *                  vectors in LDS: up to about 1.5M rows) and "fuse_dir" is
+ *                  -1, 0 never.  Not used while per-kernel timing is enabled.
+ *                  Launches of concurrent solves on one GPU take turns.
+ *   "meet_polls"   bound of a wait between those workgroups, in polls of about
+ *                  1 us (0 .. 2^21, default 2^21); a solve whose workgroups
+ *                  give up goes on with a launch per phase, from the last
+ *                  true residual
  *   "session_mode" form of the batch sessions opened afterwards: 0 (default)
  *                  per-slot recurrences up to 2 slots, the shared block above;
  *                  1 always the shared block; 2 always per slot

@@ -56,6 +56,22 @@ struct HostCSR {
 // workgroups where the product is latency-bound), two at and above it
 constexpr int64_t kOneRowMax = 250000;
 
+// Tiling of the one-launch CG chunks (cg_grid.hip): G workgroups (0: none
+// fits), each A planes by S places of the rows seen as planes of P
+constexpr int kGridBlock = 512;             // threads of a workgroup
+constexpr int kGridMaxWg = 256;             // workgroups
+constexpr int kGridSlots = kGridMaxWg + 64; // their slots and those of their groups
+constexpr int kMeetPolls = 1 << 21;         // bound of a wait between them (about 2 s)
+constexpr int kGridDiag = 7;                // upper diagonals the kernel is compiled for
+struct GridPlan {
+    int G = 0, P = 0, planes = 0, A = 0, S = 0, nS = 0, nch = 0, H = 0, pitch = 0, hcap = 0;
+    int instance = 0;
+    int wlds = 0;
+    size_t lds = 0;
+    double cost = 0;             // estimated us per iteration
+    int32_t dl[kGridDiag] = {0};
+};
+
 struct DevMatrix {
     int64_t n = 0;
     int64_t nnz = 0;        // structural nonzeros (CSR)
@@ -86,6 +102,7 @@ struct DevMatrix {
     // stored): array k = 0 .. ndiag-1 holds upper diagonal k (unrolled
     // kernels only, products of the CG iteration only)
     bool unit = false;
+    GridPlan grid64, grid32;   // one-launch CG chunks on a scaled operator
     // launch shape of the single-vector CG kernels: workgroup-sized row
     // passes per block of the FP64-vector and FP32-vector diagonal SpMV, and
     // 16-byte packs per thread of the vector updates
@@ -241,6 +258,10 @@ struct hns_operator {
     // inside the next product, p in two buffers; the same arithmetic):
     // -1 by vector size, 0 never, 1 always
     int fuse_dir = -1;
+    // scaled point-Jacobi chunks in one launch (cg_grid.hip): -1 where a
+    // plan fits and fuse_dir is automatic, 0 never
+    int one_launch = -1;
+    int meet_polls = hns::kMeetPolls;   // polls before a one-launch chunk gives up
     // batch sessions: 0 per-slot recurrences up to 2 slots, the shared
     // multi-right-hand-side block above; 1 always the block; 2 always per slot
     int session_mode = 0;

@@ -26,6 +26,7 @@ struct Scalars {
     int32_t stop;    // 0 running, 1 recursive residual below tolerance, 2 breakdown, 3 b = 0
     int32_t iter;    // CG iterations executed
     uint32_t xtoken; // tag of the last iteration whose update ran (x += alpha p pending)
+    int32_t lost;    // a one-launch chunk gave up waiting: its vectors are void
 };
 
 // Layout of the per-workspace partial-sum buffer (doubles).  The FP32 SpMV
@@ -126,6 +127,16 @@ hns_status launch_scaled_fused_close(const IterArgs &a, const void *po, uint32_t
 // boundaries (latency-bound sizes).  FP64 or FP32 (prec F64 / F32) only.
 constexpr int64_t kSmallMaxN = 1 << 20;
 hns_status launch_cg_small(const IterArgs &a, int parity, int count, hipStream_t s);
+
+// The tilings of the one-launch chunks for the scaled operator S (host work,
+// once per operator), and `count` iterations of Jacobi-scaled CG in one
+// cooperative launch: the recurrence, scalars and stopping rule of
+// launch_iteration, dot products summed by workgroup in another order.  On
+// return x, r and p are those after the chunk; a.q is scratch.  Needs the
+// plan of a.prec (G > 0).  polls: bound of each wait.  Sets Scalars::lost when the workgroups fail to
+// meet (x, r, p void).
+void grid_plans(DevMatrix &S);
+hns_status launch_cg_grid(const IterArgs &a, int parity, int count, int polls, hipStream_t s);
 
 // q = mask(A p) without reductions (residuals and hns_apply)
 hns_status launch_spmv_plain(const DevMatrix &A, bool fp32, const void *p, void *q,

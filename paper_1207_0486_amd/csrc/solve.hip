@@ -45,6 +45,7 @@ struct Workspace {
     double *mf = nullptr;         // element results of a matrix-free product (on first use)
     double *p2 = nullptr;         // second direction buffer of the fused iterations (on first use)
     bool fused = false;           // the last chunk ran fused iterations (two timed kernels)
+    bool no_grid = false;         // one-launch chunks gave up in this solve
     Scalars *sc = nullptr;        // [0] FP64 / outer loop, [1] inner FP32 loop
     Scalars *host = nullptr;      // pinned mirror of sc[0..1]
     std::vector<hipEvent_t> ev;   // timing events, a (start, end) pair per kernel of an iteration
@@ -298,6 +299,18 @@ static bool fuse_wanted(const hns_operator *op, bool fp32)
     return (size_t)op->n * (fp32 ? sizeof(float) : sizeof(double)) <= kFuseBytes;
 }
 
+// Chunks in one cooperative launch (cg_grid.hip): where the operator has a
+// plan for the precision, unless the caller asked for a form of the launches
+// per phase, times them, or a chunk of this solve gave up.
+constexpr int kGridChunk = 1024;
+
+static bool grid_wanted(const hns_operator *op, const Workspace *w, Prec prec, bool scaled)
+{
+    if (!scaled || w->no_grid || op->one_launch == 0 || op->fuse_dir >= 0) return false;
+    if (!w->borrowed && op->profile > 0) return false;
+    return prec == Prec::F32 ? op->S.grid32.G > 0 : prec == Prec::F64 && op->S.grid64.G > 0;
+}
+
 static hns_status enqueue_iterations(hns_operator *op, Workspace *w, Prec prec, int bit, void *x,
                                      void *r, void *p, void *q, const void *dinv, Scalars *sc,
                                      int count, int parity0, hipStream_t s,
@@ -325,6 +338,8 @@ static hns_status enqueue_iterations(hns_operator *op, Workspace *w, Prec prec, 
     }
     // latency-bound sizes: the whole chunk in one workgroup
     if (small_chunks(op, w, prec, lfac, ic, scaled)) return launch_cg_small(a, parity0, count, s);
+    if (grid_wanted(op, w, prec, scaled))
+        return launch_cg_grid(a, parity0, count, op->meet_polls, s);
     // sampled: the iteration in the middle of each period window, so a chunk's
     // first iteration (launched after the host's read of the previous chunk,
     // on an idle GPU) is never timed unless every iteration is
@@ -497,6 +512,7 @@ struct ChunkedSolve {
         hns_operator *op = c.op;
         Workspace *w = c.w;
         info->outer_iterations = 0;
+        w->no_grid = false;
         HNS_TRY(begin_solve(c, info));
         Scalars &h = w->host[0];
         if (!(h.bb > 0.0)) {  // b = 0
@@ -601,7 +617,8 @@ struct ChunkedSolve {
                                           : nullptr;
         const int per = small_chunks(op, w, p, lf, p == Prec::F64 ? c.ic : nullptr, c.scaled)
                             ? std::max(op->check_every, kSmallChunk)
-                            : op->check_every;
+                        : grid_wanted(op, w, p, c.scaled) ? std::max(op->check_every, kGridChunk)
+                                                          : op->check_every;
         const int chunk = std::min({c.max_iter - hr.iter, per, budget});
         if (chunk > 0 && hr.stop == 0) {
             void *x = mixed ? (void *)w->d32 : c.scaled ? (void *)w->z : (void *)c.x;
@@ -624,6 +641,16 @@ struct ChunkedSolve {
         Workspace *w = c.w;
         Scalars &h = w->host[0];
         Scalars &hr = w->host[which()];
+        if (hr.lost) {   // void vectors: again from x, with a launch per phase
+            w->no_grid = true;
+            HNS_TRY(true_residual_fp64(c));
+            HNS_TRY(pull_scalars(w, 0, c.s));
+            hr.lost = 0;
+            hr.iter = before;
+            info->iterations = before;
+            fresh = true;
+            return HNS_OK;
+        }
         since += hr.iter - before;
         HNS_TRY(account_iterations(op, w, mixed, hr.iter - before));
         if (hr.stop == 0 && hr.iter < c.max_iter) return HNS_OK;   // still running
@@ -882,6 +909,7 @@ static hns_status scaled_operator(hns_operator *op)
         (void)hipFree(w);
         return st;
     }
+    grid_plans(S);
     op->S = S;
     op->jac_s = sh;
     op->jac_w = w;
@@ -1599,6 +1627,10 @@ hns_status hns_set_param(hns_operator *op, const char *name, double value)
         op->jacobi_scaling = (int)value;
     } else if (k == "fuse_dir" && (value == -1 || value == 0 || value == 1)) {
         op->fuse_dir = (int)value;
+    } else if (k == "one_launch" && (value == -1 || value == 0)) {
+        op->one_launch = (int)value;
+    } else if (k == "meet_polls" && value >= 0 && value <= kMeetPolls && value == (int)value) {
+        op->meet_polls = (int)value;
     } else if (k == "session_mode" && (value == 0 || value == 1 || value == 2)) {
         op->session_mode = (int)value;
     } else if (k == "small_n" && value >= 0 && value <= (double)kSmallMaxN &&

@@ -202,7 +202,11 @@ struct hns_operator {
     int64_t bad_diag = -1;      // first non-positive diagonal entry, -1 if none
     int assembly = 0;           // 0 host, 1 values on the device, 2 the whole operator there
     // auxiliary forms for the step right-hand sides
+    // (the divergence forms in diagonal arrays Bdia where M takes diagonal
+    // storage: per component the diagonal, then for each offset o of M
+    // B(i, i + o), then B(i + o, i), n doubles each; else B and Bt in CSR)
     hns::DevMatrix M, B[3], Bt[3], Ms;
+    double *Bdia = nullptr;
     bool has_aux = false;
     double *step_tmp = nullptr;   // 3 n doubles of scratch for the step kernels
     // mesh on the device for the advection term (HNS_STEP_AUX): coordinates

@@ -1319,9 +1319,36 @@ static hns_status assemble_step_aux(hns_operator *op, const hns_mesh *mesh, cons
         const uint32_t fmt = choose_format(M) == HNS_FMT_SDIA ? HNS_FMT_SDIA : HNS_FMT_CSR;
         HNS_TRY(upload_matrix(M, fmt, false, op->M));
     }
+    const int64_t n = op->n;
+    const int m = op->M.fmt == HNS_FMT_SDIA && op->M.ndiag <= kMaxDiag ? op->M.ndiag : 0;
+    if (m > 0) {
+        const hipError_t e = hipMalloc((void **)&op->Bdia, 3 * (2 * (size_t)m + 1) * n * sizeof(double));
+        if (e != hipSuccess) {
+            op->Bdia = nullptr;
+            set_error("allocation of the divergence forms failed: %s", hipGetErrorString(e));
+            return e == hipErrorOutOfMemory ? HNS_ERR_OOM : HNS_ERR_HIP;
+        }
+    }
     for (int c = 0; c < 3; ++c) {
         HostCSR B, Bt;
         HNS_TRY(assemble_divergence_host(mesh, A, c, B));
+        if (m > 0) {   // the pattern of A, whose offsets are M's
+            std::vector<double> dia((2 * (size_t)m + 1) * n, 0.0);
+            for (int64_t i = 0; i < n; ++i)
+                for (int32_t t = B.rowptr[i]; t < B.rowptr[i + 1]; ++t) {
+                    const int64_t o = B.col[t] - i, row = o < 0 ? i + o : i;
+                    int k = 0;
+                    while (o != 0 && k < m && op->M.off[k] != std::abs(o)) ++k;
+                    if (k == m) {
+                        set_error("a divergence entry lies outside the mass matrix's diagonals");
+                        return HNS_ERR_INVALID;
+                    }
+                    dia[(o == 0 ? 0 : o > 0 ? 1 + k : 1 + m + k) * (size_t)n + row] = B.val[t];
+                }
+            HNS_TRY_HIP(hipMemcpy(op->Bdia + c * (2 * (size_t)m + 1) * n, dia.data(),
+                                  dia.size() * sizeof(double), hipMemcpyHostToDevice));
+            continue;
+        }
         transpose_values(B, Bt);
         HNS_TRY(upload_matrix(B, HNS_FMT_CSR, false, op->B[c]));
         HNS_TRY(upload_matrix(Bt, HNS_FMT_CSR, false, op->Bt[c]));
@@ -1526,7 +1553,7 @@ void hns_operator_destroy(hns_operator *op)
     for (auto &b : op->B) b.release();
     for (auto &b : op->Bt) b.release();
     op->Ms.release();
-    void *ptrs[] = {op->dinv,     op->dinv32,    op->bc,      op->lumped,  op->step_tmp,
+    void *ptrs[] = {op->dinv,     op->dinv32,    op->bc,      op->lumped,  op->step_tmp, op->Bdia,
                     op->mesh_xyz, op->mesh_tets, op->inc_ptr, op->inc_tet, op->inc_loc,
                     op->jac_s,    op->jac_w};
     for (void *p : ptrs)
@@ -1688,7 +1715,8 @@ size_t hns_footprint_bytes(const hns_operator *op, int k, uint32_t mode, int inc
             b += (size_t)op->A.ndiag * op->n * (op->A.dia32 ? 12 : 8) + (size_t)op->n * (8 + 4);
         if (op->dinv32) b += (size_t)op->n * 4;
         if (op->has_aux)
-            b += op->M.bytes() + op->B[0].bytes() * 6 + op->Ms.bytes() + 24 * (size_t)op->n +
+            b += op->M.bytes() + op->B[0].bytes() * 6 +
+                 (op->Bdia ? 3 * (2 * (size_t)op->M.ndiag + 1) * op->n * 8 : 0) + op->Ms.bytes() + 24 * (size_t)op->n +
                  (3 * 8 + 8) * (size_t)op->n + (4 * 4 + 4 * (4 + 1)) * (size_t)op->ntet;
     }
     return b;

@@ -19,7 +19,8 @@ LIB = os.path.join(HERE, "libhns.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
-SOURCES = ["assemble.cpp", "assemble_gpu.hip", "ic0.cpp", "kernels.hip", "cg_grid.hip", "solve.hip",
+SOURCES = ["assemble.cpp", "assemble_gpu.hip", "ic0.cpp", "kernels.hip", "cg_grid.hip",
+           "small_solve.hip", "solve.hip",
            "batched.hip", "step.hip"]
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-I", INCLUDE, "-I", CSRC,

@@ -158,14 +158,6 @@ __device__ __forceinline__ bool collect_few(const uint64_t *slots, int count, ui
     return true;
 }
 
-// Keeps the compiler from carrying what derives from v (a row's fifteen LDS
-// addresses) across iterations in registers, which the matrix needs.
-__device__ __forceinline__ int fresh(int v)
-{
-    asm volatile("" : "+v"(v));
-    return v;
-}
-
 __device__ __forceinline__ int fresh_scalar(int v)
 {
     asm volatile("" : "+s"(v));

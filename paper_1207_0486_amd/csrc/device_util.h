@@ -59,5 +59,13 @@ __device__ __forceinline__ bool is_dirichlet(const uint8_t *bc, int bit, int64_t
 __device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
 __device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 
+// Keeps the compiler from carrying what derives from v (the LDS addresses
+// of its neighbours, say) across iterations in registers, which the matrix needs.
+__device__ __forceinline__ int fresh(int v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
 }  // namespace
 }  // namespace hns

@@ -138,6 +138,27 @@ hns_status launch_cg_small(const IterArgs &a, int parity, int count, hipStream_t
 void grid_plans(DevMatrix &S);
 hns_status launch_cg_grid(const IterArgs &a, int parity, int count, int polls, hipStream_t s);
 
+// A whole FP64 point-Jacobi solve of a small operator in one launch of one
+// workgroup, or `count` iterations of it (resume: continues from r, p and *st of
+// an earlier launch with the same b, x and tolerance).  *st is device memory.
+struct SmallState {
+    enum : int32_t { kRunning, kDone, kCapped, kFloor, kBreakdown, kBadRhs, kZero };
+    double rho, gamma, bb, rr_true, rr_best, mean_b, nonfinite;
+    int32_t iter, phase, floor_checks, pad;
+};
+constexpr int kSmallSolveBlock = 512;
+constexpr int kSmallSolveDiag = 7;          // upper diagonals it is compiled for
+constexpr int64_t kSmallSolveRows = 2560;   // rows at most
+inline bool small_solve_fits(const DevMatrix &A)
+{
+    return A.fmt == HNS_FMT_SDIA && !A.unit && A.ndiag == kSmallSolveDiag &&
+           A.n <= kSmallSolveRows;
+}
+hns_status launch_small_solve(const DevMatrix &A, const double *dinv, const double *b, double *x,
+                              double *r, double *p, const uint8_t *bc, int bit, bool singular,
+                              const double *lumped, double lumped_sum, double tol, int max_iter,
+                              int count, bool resume, SmallState *st, hipStream_t s);
+
 // q = mask(A p) without reductions (residuals and hns_apply)
 hns_status launch_spmv_plain(const DevMatrix &A, bool fp32, const void *p, void *q,
                              const uint8_t *bc, int bit, hipStream_t s,

@@ -492,6 +492,8 @@ static hns_status finish_solve(const SolveCtx &c, hns_solve_info *info, hns_stat
 //    residual has dropped by `replace_drop` since the last FP64 residual, the
 //    FP32 iterate is added to the FP64 solution, the true residual is
 //    recomputed in FP64, and the recurrence continues from it.
+constexpr int kWholeIterations = 1 << 14;   // of a whole small solve per launch (about 20 ms)
+
 struct ChunkedSolve {
     SolveCtx c;
     hns_solve_info *info = nullptr;
@@ -504,15 +506,83 @@ struct ChunkedSolve {
     int since = 0, replacements = 0, stalls = 0, floor_checks = 0, before = 0;
     double tol2 = 0, drop2 = 0, rr_true = 0, bb = 0, rr_prev = 0, rr_best = INFINITY;
     const void *dinv = nullptr;
+    bool whole = false;          // one workgroup runs everything (launch_small_solve)
 
     int which() const { return mixed ? 1 : 0; }
 
-    hns_status begin()
+    // A small FP64 point-Jacobi solve: every stage in launch_small_solve,
+    // whose state between launches lies in the workspace's partial sums
+    static bool whole_wanted(const SolveCtx &c, Prec prec)
+    {
+        const hns_operator *op = c.op;
+        return prec == Prec::F64 && op->n <= kSmallSolveRows && small_solve_fits(op->A) &&
+               small_chunks(op, c.w, prec, c.lfac, c.ic, c.scaled);
+    }
+
+    hns_status whole_launch(int count, bool resume)
+    {
+        hns_operator *op = c.op;
+        Workspace *w = c.w;
+        static_assert(sizeof(SmallState) <= sizeof(Scalars), "read into the scalars' mirror");
+        SmallState *st = reinterpret_cast<SmallState *>(w->partials);
+        HNS_TRY(launch_small_solve(op->A, op->dinv, c.b, c.x, w->r, w->p, op->bc, c.bit,
+                                   c.singular, op->lumped, op->lumped_sum, c.tol, c.max_iter,
+                                   count, resume, st, c.s));
+        HNS_TRY_HIP(hipMemcpyAsync(&w->host[1], st, sizeof(SmallState), hipMemcpyDeviceToHost,
+                                   c.s));
+        return HNS_OK;
+    }
+
+    // what a completed launch came to
+    hns_status whole_read()
+    {
+        SmallState st;
+        memcpy(&st, &c.w->host[1], sizeof(st));
+        c.w->host[0].iter = st.iter;
+        info->iterations = st.iter;
+        info->removed_mean = st.mean_b;
+        info->outer_iterations = st.phase == SmallState::kZero ? 0 : 1;
+        zero_b = st.phase == SmallState::kZero;
+        rr_true = st.rr_true;
+        bb = st.bb;
+        finished = st.phase != SmallState::kRunning;
+        switch (st.phase) {
+        case SmallState::kBadRhs:
+            set_error("right-hand side has %.0f non-finite entries", st.nonfinite);
+            info->removed_mean = 0.0;
+            info->outer_iterations = 0;
+            return HNS_ERR_INVALID;
+        case SmallState::kBreakdown:
+            set_error("CG breakdown after %d iterations (p^T A p = %g)", st.iter, st.gamma);
+            status = HNS_ERR_BREAKDOWN;
+            break;
+        case SmallState::kFloor:
+            set_error("true residual stalled at %g, above the tolerance (rounding floor)",
+                      std::sqrt(rr_true / bb));
+            status = HNS_NOT_CONVERGED;
+            break;
+        case SmallState::kCapped: status = HNS_NOT_CONVERGED; break;
+        case SmallState::kRunning: break;
+        default: status = HNS_OK; break;
+        }
+        return HNS_OK;
+    }
+
+    // first: iterations that a whole solve may run at once (a caller that
+    // advances the solve itself: none)
+    hns_status begin(int first = 0)
     {
         hns_operator *op = c.op;
         Workspace *w = c.w;
         info->outer_iterations = 0;
         w->no_grid = false;
+        whole = !mixed && whole_wanted(c, prec);
+        if (whole) {
+            memset(&w->host[0], 0, sizeof(Scalars));
+            HNS_TRY(whole_launch(first, false));
+            HNS_TRY_HIP(hipStreamSynchronize(c.s));
+            return whole_read();
+        }
         HNS_TRY(begin_solve(c, info));
         Scalars &h = w->host[0];
         if (!(h.bb > 0.0)) {  // b = 0
@@ -608,6 +678,7 @@ struct ChunkedSolve {
     {
         hns_operator *op = c.op;
         Workspace *w = c.w;
+        if (whole) return whole_launch(std::min(budget, kWholeIterations), true);
         if (fresh) HNS_TRY(start_segment());
         Scalars &hr = w->host[which()];
         before = hr.iter;
@@ -639,6 +710,7 @@ struct ChunkedSolve {
     {
         hns_operator *op = c.op;
         Workspace *w = c.w;
+        if (whole) return whole_read();
         Scalars &h = w->host[0];
         Scalars &hr = w->host[which()];
         if (hr.lost) {   // void vectors: again from x, with a launch per phase
@@ -755,6 +827,11 @@ struct ChunkedSolve {
 
     hns_status end()
     {
+        if (whole) {   // normalised and synchronised already
+            info->relres_true = bb > 0 ? std::sqrt(rr_true / bb) : 0.0;
+            info->status = status;
+            return status;
+        }
         if (!zero_b) {
             if (mixed) {
                 info->outer_iterations = replacements;
@@ -772,7 +849,7 @@ struct ChunkedSolve {
 
 static hns_status run_to_end(ChunkedSolve &cs)
 {
-    HNS_TRY(cs.begin());
+    HNS_TRY(cs.begin(kWholeIterations));
     while (!cs.finished) {
         HNS_TRY(cs.enqueue(INT_MAX));
         HNS_TRY_HIP(hipStreamSynchronize(cs.c.s));

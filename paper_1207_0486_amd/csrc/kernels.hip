@@ -2004,9 +2004,11 @@ int sdia_dispatch(const DevMatrix &A, const TV *vals, const void *p, void *q, co
 // (grad u)_d = sum_s du/ds_s adj(J)_sd / det: the element matrix of the
 // assembled operator applied to x_e, evaluated by sum factorisation (the
 // tensor-product basis contracted one direction at a time, forward to the
-// Gauss points and back).  One thread per Gauss point / local node, an
-// element per (order+1)^3 lanes of a wavefront, the contractions through
-// LDS.  Element results go to a scratch array at node-ordered positions (a
+// Gauss points and back).  A lane holds a line of points in direction 2, an
+// element (order+1)^2 lanes of one wavefront (7 Q2 or 16 Q1 elements each):
+// direction 2 is contracted in registers with weights from scalars, the Jacobian's
+// face values are formed once per line, and only directions 0 and 1 cross lanes,
+// through LDS.  Element results go to a scratch array at node-ordered positions (a
 // node's contributions contiguous, in ascending element order); a second
 // kernel sums each node's run (deterministic), zeroes Dirichlet rows and
 // forms the p^T q partials.
@@ -2028,6 +2030,12 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Bound by latency and FP64 work at two wavefronts per SIMD.  With a lane per
+// Gauss point it was bound by LDS (some 120 reads of 8 bytes per point: tables,
+// corners and neighbours; 24 now): the product with its gather, 163,840 Q2 elements,
+// 119 -> 84 us; 1.31M Q1 elements 228 -> 180 us, 163,840 of them 49 -> 45.  Three or
+// four wavefronts per SIMD spill (28 and 72 registers) and were slower: the solve
+// 3.6 ms with two, 3.9 with three, 5.7 with four.
 template <int P>
 __global__ __launch_bounds__(kBlock) void k_mf_element(int64_t ne,
                                                        const int32_t *__restrict__ nodes,
@@ -2037,12 +2045,12 @@ __global__ __launch_bounds__(kBlock) void k_mf_element(int64_t ne,
                                                        double *__restrict__ Y,
                                                        const Scalars *__restrict__ sc)
 {
-    constexpr int Q = P + 1, NL = Q * Q * Q, EW = 64 / NL, EB = (kBlock / 64) * EW;
+    constexpr int Q = P + 1, LW = Q * Q, NL = Q * LW;
+    constexpr int W = kBlock / 64, EW = 64 / LW, EB = W * EW;
     if (sc && sc->stop) return;
     __shared__ double sV[3][3], sD[3][3], sLV[2][3], sLD[2][3], sW[3];
-    __shared__ double a0[EB][NL], a1[EB][NL], a2[EB][NL], a3[EB][NL];
-    __shared__ double b0[EB][NL], b1[EB][NL], b2[EB][NL];
-    __shared__ double sX[EB][24];
+    __shared__ double sh[W][3 * Q][64];              // a value per lane and array
+    __shared__ __align__(16) double sX[W][EW][24];   // the elements' corners
     if (threadIdx.x < 9) {
         sV[threadIdx.x / 3][threadIdx.x % 3] = T.V[threadIdx.x / 3][threadIdx.x % 3];
         sD[threadIdx.x / 3][threadIdx.x % 3] = T.D[threadIdx.x / 3][threadIdx.x % 3];
@@ -2053,160 +2061,209 @@ __global__ __launch_bounds__(kBlock) void k_mf_element(int64_t ne,
     } else if (threadIdx.x < 18) {
         sW[threadIdx.x - 15] = T.gw[threadIdx.x - 15];
     }
-    const int lane = threadIdx.x & 63;
-    const int slot = lane / NL, t = lane - slot * NL;
-    const int es = (threadIdx.x >> 6) * EW + slot;   // element slot of the block
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int slot = lane / LW, t = lane - slot * LW;
     const bool on = slot < EW;
-    const int t0 = t % Q, t1 = (t / Q) % Q, t2 = t / (Q * Q);
+    const int t0 = t % Q, t1 = t / Q;
+    const int r0 = lane - t0, r1 = lane - Q * t1;   // the first lane of the line in direction 0, 1
     const double cm = T.coef[0], cs = T.coef[1];
     const double nu[3] = {T.coef[2], T.coef[3], T.coef[4]};
     __syncthreads();   // the tables; below, every element lives in one wavefront
     // the next group's x values and corners are loaded into registers while
     // the current group computes (a workgroup takes several groups in turn)
-    constexpr int NC = (24 + NL - 1) / NL;   // corner values per lane
+    constexpr int NC = (24 + LW - 1) / LW;   // corner values per lane
     const int64_t stride = (int64_t)gridDim.x * EB;
-    double px = 0.0, pc[NC];
+    double px[Q], pc[NC];
+#pragma unroll
+    for (int k = 0; k < Q; ++k) px[k] = 0.0;
 #pragma unroll
     for (int k = 0; k < NC; ++k) pc[k] = 0.0;
     auto fetch = [&](int64_t e) {
         if (on && e < ne) {
-            px = x[nodes[e * NL + t]];
+#pragma unroll
+            for (int k = 0; k < Q; ++k) px[k] = x[nodes[e * NL + k * LW + t]];
 #pragma unroll
             for (int k = 0; k < NC; ++k)
-                if (t + k * NL < 24) pc[k] = corner[e * 24 + t + k * NL];
+                if (t + k * LW < 24) pc[k] = corner[e * 24 + t + k * LW];
         }
     };
+    const int es = w * EW + slot;   // element slot of the block
     fetch((int64_t)blockIdx.x * EB + es);
     for (int64_t e0 = (int64_t)blockIdx.x * EB; e0 < ne; e0 += stride) {
         const int64_t e = e0 + es;
         const bool act = on && e < ne;
-        int32_t out = 0;
+        int32_t out[Q];
         if (act) {
-            a0[es][t] = px;
+#pragma unroll
+            for (int k = 0; k < Q; ++k) sh[w][k][lane] = px[k];
 #pragma unroll
             for (int k = 0; k < NC; ++k)
-                if (t + k * NL < 24) sX[es][t + k * NL] = pc[k];
-            out = pos[e * NL + t];
+                if (t + k * LW < 24) sX[w][slot][t + k * LW] = pc[k];
+#pragma unroll
+            for (int k = 0; k < Q; ++k) out[k] = pos[e * NL + k * LW + t];
         }
         fetch(e + stride);
         wave_lds_sync();
-        // forward, direction 0: thread (g0 = t0, a1 = t1, a2 = t2)
+        // forward, direction 0: lane (g0 = t0, a1 = t1), values at a2 = k
+        double v[Q], d[Q];
         if (act) {
-            double v = 0.0, d = 0.0;
+#pragma unroll
+            for (int k = 0; k < Q; ++k) v[k] = d[k] = 0.0;
 #pragma unroll
             for (int a = 0; a < Q; ++a) {
-                const double xa = a0[es][a + Q * t1 + Q * Q * t2];
-                v += sV[a][t0] * xa;
-                d += sD[a][t0] * xa;
+                const double wv = sV[a][t0], wd = sD[a][t0];
+#pragma unroll
+                for (int k = 0; k < Q; ++k) {
+                    const double xa = sh[w][k][r0 + a];
+                    v[k] += wv * xa;
+                    d[k] += wd * xa;
+                }
             }
-            b0[es][t] = v;
-            b1[es][t] = d;
         }
         wave_lds_sync();
-        // direction 1: thread (g0, g1 = t1, a2)
         if (act) {
-            double vv = 0.0, vd = 0.0, dv = 0.0;
 #pragma unroll
-            for (int a = 0; a < Q; ++a) {
-                const int k = t0 + Q * a + Q * Q * t2;
-                vv += sV[a][t1] * b0[es][k];
-                vd += sD[a][t1] * b0[es][k];
-                dv += sV[a][t1] * b1[es][k];
+            for (int k = 0; k < Q; ++k) {
+                sh[w][k][lane] = v[k];
+                sh[w][Q + k][lane] = d[k];
             }
-            a1[es][t] = vv;
-            a2[es][t] = vd;
-            a3[es][t] = dv;
         }
         wave_lds_sync();
-        // direction 2, then the point's geometry and fluxes: thread g = t
+        // direction 1 (g1 = t1), then direction 2 and the points' geometry and
+        // fluxes along the lane's line, their way back in direction 2 with them
+        double ra[Q], rb[Q], rc[Q];
         if (act) {
-            double u = 0.0, us[3] = {0.0, 0.0, 0.0};
+            double vv[Q], vd[Q], dv[Q];
+#pragma unroll
+            for (int k = 0; k < Q; ++k) vv[k] = vd[k] = dv[k] = ra[k] = rb[k] = rc[k] = 0.0;
 #pragma unroll
             for (int a = 0; a < Q; ++a) {
-                const int k = t0 + Q * t1 + Q * Q * a;
-                u += sV[a][t2] * a1[es][k];
-                us[2] += sD[a][t2] * a1[es][k];
-                us[1] += sV[a][t2] * a2[es][k];
-                us[0] += sV[a][t2] * a3[es][k];
+                const double wv = sV[a][t1], wd = sD[a][t1];
+#pragma unroll
+                for (int k = 0; k < Q; ++k) {
+                    const double va = sh[w][k][r1 + Q * a], da = sh[w][Q + k][r1 + Q * a];
+                    vv[k] += wv * va;
+                    vd[k] += wd * va;
+                    dv[k] += wv * da;
+                }
             }
-            // J[r][d] = d x_r / d s_d from the 8 corners
-            double J[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+            // d x_r / d s_0, d x_r / d s_1 and x_r on the faces c2 = 0, 1 (at this
+            // line's s_0, s_1): the Jacobian is linear between them
+            double B0[3][2], B1[3][2], BX[3][2];
+#pragma unroll
+            for (int r = 0; r < 3; ++r)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) B0[r][c] = B1[r][c] = BX[r][c] = 0.0;
 #pragma unroll
             for (int c = 0; c < 8; ++c) {
                 const int c0 = c & 1, c1 = (c >> 1) & 1, c2 = c >> 2;
-                const double g0 = sLD[c0][t0] * sLV[c1][t1] * sLV[c2][t2];
-                const double g1 = sLV[c0][t0] * sLD[c1][t1] * sLV[c2][t2];
-                const double g2 = sLV[c0][t0] * sLV[c1][t1] * sLD[c2][t2];
+                const double g0 = sLD[c0][t0] * sLV[c1][t1];
+                const double g1 = sLV[c0][t0] * sLD[c1][t1];
+                const double gx = sLV[c0][t0] * sLV[c1][t1];
 #pragma unroll
                 for (int r = 0; r < 3; ++r) {
-                    const double X = sX[es][3 * c + r];
-                    J[r][0] += X * g0;
-                    J[r][1] += X * g1;
-                    J[r][2] += X * g2;
+                    const double X = sX[w][slot][3 * c + r];
+                    B0[r][c2] += X * g0;
+                    B1[r][c2] += X * g1;
+                    BX[r][c2] += X * gx;
                 }
             }
-            double A[3][3];
-            A[0][0] = J[1][1] * J[2][2] - J[1][2] * J[2][1];
-            A[0][1] = J[0][2] * J[2][1] - J[0][1] * J[2][2];
-            A[0][2] = J[0][1] * J[1][2] - J[0][2] * J[1][1];
-            A[1][0] = J[1][2] * J[2][0] - J[1][0] * J[2][2];
-            A[1][1] = J[0][0] * J[2][2] - J[0][2] * J[2][0];
-            A[1][2] = J[0][2] * J[1][0] - J[0][0] * J[1][2];
-            A[2][0] = J[1][0] * J[2][1] - J[1][1] * J[2][0];
-            A[2][1] = J[0][1] * J[2][0] - J[0][0] * J[2][1];
-            A[2][2] = J[0][0] * J[1][1] - J[0][1] * J[1][0];
-            const double det = J[0][0] * A[0][0] + J[0][1] * A[1][0] + J[0][2] * A[2][0];
-            const double w = sW[t0] * sW[t1] * sW[t2];
-            const double inv = 1.0 / det;
-            double f[3];
-#pragma unroll
-            for (int d = 0; d < 3; ++d)
-                f[d] = nu[d] * ((us[0] * A[0][d] + us[1] * A[1][d] + us[2] * A[2][d]) * inv);
-            // mass and reference fluxes at the point (arrays free since the
-            // forward pass of direction 1): M -> b0, F_0 -> b1, F_1 -> b2, F_2 -> a0
-            b0[es][t] = w * det * cm * u;
-            b1[es][t] = w * cs * (A[0][0] * f[0] + A[0][1] * f[1] + A[0][2] * f[2]);
-            b2[es][t] = w * cs * (A[1][0] * f[0] + A[1][1] * f[1] + A[1][2] * f[2]);
-            a0[es][t] = w * cs * (A[2][0] * f[0] + A[2][1] * f[1] + A[2][2] * f[2]);
-        }
-        wave_lds_sync();
-        // back, direction 2: thread (g0, g1, a2 = t2)
-        if (act) {
-            double ra = 0.0, rb = 0.0, rc = 0.0;
+            const double w01 = sW[t0] * sW[t1];
 #pragma unroll
             for (int g = 0; g < Q; ++g) {
-                const int k = t0 + Q * t1 + Q * Q * g;
-                ra += sV[t2][g] * b0[es][k] + sD[t2][g] * a0[es][k];
-                rb += sV[t2][g] * b2[es][k];
-                rc += sV[t2][g] * b1[es][k];
+                double u = 0.0, us[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+                for (int a = 0; a < Q; ++a) {
+                    u += T.V[a][g] * vv[a];
+                    us[2] += T.D[a][g] * vv[a];
+                    us[1] += T.V[a][g] * vd[a];
+                    us[0] += T.V[a][g] * dv[a];
+                }
+                double J[3][3];   // J[r][d] = d x_r / d s_d
+#pragma unroll
+                for (int r = 0; r < 3; ++r) {
+                    J[r][0] = B0[r][0] * T.LV[0][g] + B0[r][1] * T.LV[1][g];
+                    J[r][1] = B1[r][0] * T.LV[0][g] + B1[r][1] * T.LV[1][g];
+                    J[r][2] = BX[r][0] * T.LD[0][g] + BX[r][1] * T.LD[1][g];
+                }
+                double A[3][3];
+                A[0][0] = J[1][1] * J[2][2] - J[1][2] * J[2][1];
+                A[0][1] = J[0][2] * J[2][1] - J[0][1] * J[2][2];
+                A[0][2] = J[0][1] * J[1][2] - J[0][2] * J[1][1];
+                A[1][0] = J[1][2] * J[2][0] - J[1][0] * J[2][2];
+                A[1][1] = J[0][0] * J[2][2] - J[0][2] * J[2][0];
+                A[1][2] = J[0][2] * J[1][0] - J[0][0] * J[1][2];
+                A[2][0] = J[1][0] * J[2][1] - J[1][1] * J[2][0];
+                A[2][1] = J[0][1] * J[2][0] - J[0][0] * J[2][1];
+                A[2][2] = J[0][0] * J[1][1] - J[0][1] * J[1][0];
+                const double det = J[0][0] * A[0][0] + J[0][1] * A[1][0] + J[0][2] * A[2][0];
+                const double wt = w01 * T.gw[g];
+                const double inv = 1.0 / det;
+                double f[3];
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+                    f[q] = nu[q] * ((us[0] * A[0][q] + us[1] * A[1][q] + us[2] * A[2][q]) * inv);
+                // mass and reference fluxes at the point
+                const double m = wt * det * cm * u;
+                const double F0 = wt * cs * (A[0][0] * f[0] + A[0][1] * f[1] + A[0][2] * f[2]);
+                const double F1 = wt * cs * (A[1][0] * f[0] + A[1][1] * f[1] + A[1][2] * f[2]);
+                const double F2 = wt * cs * (A[2][0] * f[0] + A[2][1] * f[1] + A[2][2] * f[2]);
+#pragma unroll
+                for (int a = 0; a < Q; ++a) {
+                    ra[a] += T.V[a][g] * m + T.D[a][g] * F2;
+                    rb[a] += T.V[a][g] * F1;
+                    rc[a] += T.V[a][g] * F0;
+                }
             }
-            a1[es][t] = ra;
-            a2[es][t] = rb;
-            a3[es][t] = rc;
         }
         wave_lds_sync();
-        // direction 1: thread (g0, a1 = t1, a2)
         if (act) {
-            double sa = 0.0, sc2 = 0.0;
 #pragma unroll
-            for (int g = 0; g < Q; ++g) {
-                const int k = t0 + Q * g + Q * Q * t2;
-                sa += sV[t1][g] * a1[es][k] + sD[t1][g] * a2[es][k];
-                sc2 += sV[t1][g] * a3[es][k];
+            for (int k = 0; k < Q; ++k) {
+                sh[w][k][lane] = ra[k];
+                sh[w][Q + k][lane] = rb[k];
+                sh[w][2 * Q + k][lane] = rc[k];
             }
-            b0[es][t] = sa;
-            b1[es][t] = sc2;
         }
         wave_lds_sync();
-        // direction 0: thread (a0 = t0, a1, a2): the element's y at node t
+        // back, direction 1: lane (g0, a1 = t1)
+        double sa[Q], sb[Q];
         if (act) {
-            double y = 0.0;
+#pragma unroll
+            for (int k = 0; k < Q; ++k) sa[k] = sb[k] = 0.0;
 #pragma unroll
             for (int g = 0; g < Q; ++g) {
-                const int k = g + Q * t1 + Q * Q * t2;
-                y += sV[t0][g] * b0[es][k] + sD[t0][g] * b1[es][k];
+                const double wv = sV[t1][g], wd = sD[t1][g];
+#pragma unroll
+                for (int k = 0; k < Q; ++k) {
+                    sa[k] += wv * sh[w][k][r1 + Q * g] + wd * sh[w][Q + k][r1 + Q * g];
+                    sb[k] += wv * sh[w][2 * Q + k][r1 + Q * g];
+                }
             }
-            Y[out] = y;
+        }
+        wave_lds_sync();
+        if (act) {
+#pragma unroll
+            for (int k = 0; k < Q; ++k) {
+                sh[w][k][lane] = sa[k];
+                sh[w][Q + k][lane] = sb[k];
+            }
+        }
+        wave_lds_sync();
+        // direction 0: the element's y at the lane's nodes (t0, t1, k)
+        if (act) {
+            double y[Q];
+#pragma unroll
+            for (int k = 0; k < Q; ++k) y[k] = 0.0;
+#pragma unroll
+            for (int g = 0; g < Q; ++g) {
+                const double wv = sV[t0][g], wd = sD[t0][g];
+#pragma unroll
+                for (int k = 0; k < Q; ++k)
+                    y[k] += wv * sh[w][k][r0 + g] + wd * sh[w][Q + k][r0 + g];
+            }
+#pragma unroll
+            for (int k = 0; k < Q; ++k) Y[out[k]] = y[k];
         }
         wave_lds_sync();
     }
@@ -2246,7 +2303,7 @@ int mf_launch_p(const DevMatrix &A, const double *x, double *y, const uint8_t *b
                 const Scalars *sc, double *part, double *scratch, hipStream_t s,
                 hipEvent_t *ev2)
 {
-    constexpr int NL = (P + 1) * (P + 1) * (P + 1), EB = (kBlock / 64) * (64 / NL);
+    constexpr int EB = (kBlock / 64) * (64 / ((P + 1) * (P + 1)));
     MfTables T;
     for (int a = 0; a < 3; ++a)
         for (int g = 0; g < 3; ++g) {
@@ -2260,10 +2317,11 @@ int mf_launch_p(const DevMatrix &A, const double *x, double *y, const uint8_t *b
         }
     for (int g = 0; g < 3; ++g) T.gw[g] = A.mf_gw[g];
     for (int k = 0; k < 5; ++k) T.coef[k] = A.mf_coef[k];
-    // about two workgroups per SIMD's share of the chip at a time, each taking
-    // several groups of elements in turn (the loads of the next overlap)
+    // Q2: the two workgroups a CU holds at 180 registers, each taking groups of
+    // elements in turn while the next one's loads are under way (solve of 163,840
+    // elements: 512 workgroups 3553 us, 256 4334, 1024 3587, 2048 3687)
     const int64_t blocks = (A.mf_ne + EB - 1) / EB;
-    const int Ge = (int)std::max<int64_t>(1, std::min<int64_t>(blocks, 2048));
+    const int Ge = (int)std::max<int64_t>(1, std::min<int64_t>(blocks, P == 2 ? 512 : 2048));
     const int Gg = stream_grid(A.n);
     hipEvent_t e1[2] = {ev2 ? ev2[0] : nullptr, nullptr};
     hipEvent_t e2[2] = {nullptr, ev2 ? ev2[1] : nullptr};

@@ -1237,35 +1237,38 @@ __global__ __launch_bounds__(kBlock) void k_init_dir(int64_t n, TX *__restrict__
 // coalesced loads, one lane per column runs the two recurrences, and the
 // result goes back to HBM coalesced.
 
-// Thomas recurrences of the columns staged in LDS: sr holds r (read), se, sw
-// the factors, sy receives z; returns this lane's share of r^T z.
-// The four arrays are disjoint regions of the block's LDS (restrict lets the
-// loads of later steps, which do not depend on the recurrence, issue ahead of
-// the earlier steps' stores; the unrolled loops give them room to).
+// Thomas recurrences of the columns staged in LDS: sr holds r and receives z, se,
+// sw the factors; returns this lane's share of r^T z.  With t_k = r_k - e_{k-1}
+// y_{k-1} (y_k = t_k w_k), r^T z = sum t_k y_k: r is not needed on the way back, so
+// y takes its place and a block stages three arrays.  With a fourth for y a CU held
+// three blocks of 64 columns of 21 rows, and the 1040 of 256 x 256 cells needed a
+// second turn of the chip, a third full; it holds five now (k_update_line 16.6 ->
+// 14.7 us, the FP64 solve 80.5 -> 77.2 ms).
 // T = double (FP64 solves) or float (the inner iterations of mixed precision;
 // r^T z is always summed in FP64).
 template <typename T>
-__device__ __forceinline__ double line_columns(int ncols, int L, const T *__restrict__ sr,
+__device__ __forceinline__ double line_columns(int ncols, int L, T *__restrict__ sr,
                                                const T *__restrict__ se,
-                                               const T *__restrict__ sw, T *__restrict__ sy)
+                                               const T *__restrict__ sw)
 {
     double rz = 0.0;
     if ((int)threadIdx.x < ncols) {
         const int b = threadIdx.x * L;
-        T y = sr[b] * sw[b];
-        sy[b] = y;
+        T t = sr[b], y = t * sw[b];
+        rz += (double)t * (double)y;
+        sr[b] = y;
 #pragma unroll 4
         for (int k = 1; k < L; ++k) {
-            y = (sr[b + k] - se[b + k - 1] * y) * sw[b + k];
-            sy[b + k] = y;
+            t = sr[b + k] - se[b + k - 1] * y;
+            y = t * sw[b + k];
+            rz += (double)t * (double)y;
+            sr[b + k] = y;
         }
         T z = y;
-        rz += (double)sr[b + L - 1] * (double)z;
 #pragma unroll 4
         for (int k = L - 2; k >= 0; --k) {
-            z = sy[b + k] - (se[b + k] * sw[b + k]) * z;
-            sy[b + k] = z;
-            rz += (double)sr[b + k] * (double)z;
+            z = sr[b + k] - (se[b + k] * sw[b + k]) * z;
+            sr[b + k] = z;
         }
     }
     return rz;
@@ -1283,7 +1286,7 @@ struct LinePacks {
 
 constexpr int kLineLds = 49152;   // bytes of LDS for the staged columns of one block
 // rows of a block's columns a thread stages at most: a block stages at most
-// kLineLds / (4 * 8) rows (4 FP64-sized arrays of its rows in LDS)
+// kLineLds / (4 * 8) rows (three FP64-sized arrays of them in LDS)
 constexpr int kLineStage = (kLineLds / (4 * 8) + kBlock - 1) / kBlock;
 
 // r -= alpha q; z = M^-1 r; partials of r^T z and r^T r.  Block 0 records
@@ -1296,7 +1299,7 @@ __global__ __launch_bounds__(kBlock) void k_update_line(
 {
     extern __shared__ double line_lds[];
     const int span = NC * L;   // at most kLineStage * kBlock rows (NC from kLineLds)
-    T *sr = reinterpret_cast<T *>(line_lds), *se = sr + span, *sw = se + span, *sy = sw + span;
+    T *sr = reinterpret_cast<T *>(line_lds), *se = sr + span, *sw = se + span;
     const int64_t row0 = (int64_t)xcd_block(blockIdx.x, gridDim.x) * span;
     const int64_t left = n - row0;
     const int rows = left <= 0 ? 0 : (left < span ? (int)left : span);
@@ -1350,9 +1353,9 @@ __global__ __launch_bounds__(kBlock) void k_update_line(
         }
     }
     __syncthreads();
-    const double rz = line_columns<T>(rows / L, L, sr, se, sw, sy);
+    const double rz = line_columns<T>(rows / L, L, sr, se, sw);
     __syncthreads();
-    for (int t = threadIdx.x; t < rows; t += kBlock) z[row0 + t] = sy[t];
+    for (int t = threadIdx.x; t < rows; t += kBlock) z[row0 + t] = sr[t];
     double v[2] = {rz, rr};
     store_block_partials<2>(v, part_out);
 }
@@ -1429,7 +1432,7 @@ __global__ __launch_bounds__(kBlock) void k_init_line(int64_t n, int L, int NC,
     extern __shared__ double line_lds[];
     const T mean = singular ? (T)(sc->sum_r / (double)n) : (T)0;
     const int span = NC * L;
-    T *sr = reinterpret_cast<T *>(line_lds), *se = sr + span, *sw = se + span, *sy = sw + span;
+    T *sr = reinterpret_cast<T *>(line_lds), *se = sr + span, *sw = se + span;
     const int64_t row0 = (int64_t)blockIdx.x * span;
     const int64_t left = n - row0;
     const int rows = left <= 0 ? 0 : (left < span ? (int)left : span);
@@ -1448,9 +1451,9 @@ __global__ __launch_bounds__(kBlock) void k_init_line(int64_t n, int L, int NC,
         rr += (double)ri * (double)ri;
     }
     __syncthreads();
-    const double rz = line_columns<T>(rows / L, L, sr, se, sw, sy);
+    const double rz = line_columns<T>(rows / L, L, sr, se, sw);
     __syncthreads();
-    for (int t = threadIdx.x; t < rows; t += kBlock) p[row0 + t] = sy[t];
+    for (int t = threadIdx.x; t < rows; t += kBlock) p[row0 + t] = sr[t];
     double v[2] = {rz, rr};
     store_block_partials<2>(v, partials);
 }
@@ -1468,7 +1471,7 @@ __global__ __launch_bounds__(kBlock) void k_replace_line(int64_t n, int L, int N
 {
     extern __shared__ double line_lds[];
     const int span = NC * L;
-    T *sr = reinterpret_cast<T *>(line_lds), *se = sr + span, *sw = se + span, *sy = sw + span;
+    T *sr = reinterpret_cast<T *>(line_lds), *se = sr + span, *sw = se + span;
     const int64_t row0 = (int64_t)xcd_block(blockIdx.x, gridDim.x) * span;
     const int64_t left = n - row0;
     const int rows = left <= 0 ? 0 : (left < span ? (int)left : span);
@@ -1484,9 +1487,9 @@ __global__ __launch_bounds__(kBlock) void k_replace_line(int64_t n, int L, int N
         rr += (double)ri * (double)ri;
     }
     __syncthreads();
-    const double rz = line_columns<T>(rows / L, L, sr, se, sw, sy);
+    const double rz = line_columns<T>(rows / L, L, sr, se, sw);
     __syncthreads();
-    for (int t = threadIdx.x; t < rows; t += kBlock) z[row0 + t] = sy[t];
+    for (int t = threadIdx.x; t < rows; t += kBlock) z[row0 + t] = sr[t];
     double v[2] = {rz, rr};
     store_block_partials<2>(v, part_out);
 }
@@ -2423,7 +2426,7 @@ hns_status line_iteration(const IterArgs &a, int parity, hipStream_t s, hipEvent
     const int Gs = spmv_dispatch<T, T, true>(*a.A, a.p, a.q, bc, a.bit, a.sc, P1, s,
                                              ev ? ev : nullptr, a.mf);
     if (Gs < 0) return spmv_failed("spmv");
-    HNS_TRY_HIP(launch_k(k_update_line<T>, Gl, kBlock, (size_t)4 * NC * L * sizeof(T), s,
+    HNS_TRY_HIP(launch_k(k_update_line<T>, Gl, kBlock, (size_t)3 * NC * L * sizeof(T), s,
                          ev ? ev + 2 : nullptr, a.n, L, NC, (T *)a.r, (const T *)a.q, (T *)a.z,
                          (const T *)a.lfac, a.sc, (const double *)P1, Gs, P2, parity, a.token));
     HNS_TRY(launch_pupdate_line_x<T>(a, parity, Gl, s, ev ? ev + 4 : nullptr));
@@ -2729,7 +2732,7 @@ static hns_status init_line_t(int64_t n, int line_len, T *r, T *p, const T *lfac
 {
     const int NC = line_cols_per_block(line_len);
     const int G = line_grid(n, line_len);
-    k_init_line<T><<<G, kBlock, (size_t)4 * NC * line_len * sizeof(T), s>>>(
+    k_init_line<T><<<G, kBlock, (size_t)3 * NC * line_len * sizeof(T), s>>>(
         n, line_len, NC, r, p, lfac, singular ? 1 : 0, sc, partials + kPartMisc);
     HNS_TRY(check_launch("init_line"));
     k_fin_start<<<1, kBlock, 0, s>>>(partials + kPartMisc, G, sc, bb_from_rr ? 1 : 0);
@@ -2757,7 +2760,7 @@ hns_status launch_replace_line(int64_t n, int line_len, const double *r64, float
     const int NC = line_cols_per_block(line_len);
     const int G = line_grid(n, line_len);
     double *P2 = partials + kPartUpdate;
-    k_replace_line<float><<<G, kBlock, (size_t)4 * NC * line_len * sizeof(float), s>>>(
+    k_replace_line<float><<<G, kBlock, (size_t)3 * NC * line_len * sizeof(float), s>>>(
         n, line_len, NC, r64, r, z, lfac, P2);
     HNS_TRY(check_launch("replace_line"));
     // p and z are workspace vectors (16-byte aligned)

@@ -486,9 +486,10 @@ def bench_shard_share(torch, log, iters=400, reps=3):
     blocks, stood in for by a 128x64x20 basin (the same 176,085 rows and
     15-point stencil; its cells are twice as long in x): the pressure recurrence's time
     per iteration (`iters` iterations from x0 = 0, median of `reps`), FP64
-    and mixed, in two launches per iteration (the default at this size) and
-    in three: the per-GPU floor a multi-GPU split would add its halo
-    exchange and all-reduces to."""
+    and mixed, in two launches per iteration and in three: the per-GPU floor
+    a multi-GPU split would add its halo exchange and all-reduces to.  Also the
+    default of one GPU alone, chunks in one launch, which leave a split no point
+    at which to exchange."""
     import basin
     from paper_1207_0486_amd.hns import Operator
     wl = basin.configs.BASIN_256x256x20
@@ -499,7 +500,9 @@ def bench_shard_share(torch, log, iters=400, reps=3):
                        "basin256x256x20)",
            "nodes": m.n, "iterations": iters}
     for mode in ("fp64", "mixed"):
-        for label, fuse in (("two_launches", -1), ("three_launches", 0)):
+        for label, one, fuse in (("one_launch", -1, -1), ("two_launches", 0, -1),
+                                 ("three_launches", 0, 0)):
+            op.set_param("one_launch", one)
             op.set_param("fuse_dir", fuse)
             ts = []
             for k in range(reps + 1):
@@ -1201,7 +1204,8 @@ def main():
     log(f"fp64: {ms64:.1f} ms/step, {gbs64:.0f} GB/s, iters "
         + ", ".join(f"{k}={i.iterations}" for k, i in infos64.items()))
 
-    # dominant kernel: the SpMV of the pressure solve, timed live with HIP events
+    # the largest kernel of the launch-per-phase path, the SpMV of the pressure
+    # solve, timed with HIP events in the step that follows the timed ones
     spmv_ms, spmv_n = prof64["pois"]["spmv"]
     if spmv_n == 0:
         raise RuntimeError("no pressure-solve SpMV launch was timed")
@@ -1376,6 +1380,7 @@ def main():
         "errors_vs_oracle": errors,
         "step_ms": [round(1e3 * v, 3) for v in per64],
         "roofline": {"bound": "hbm", "achieved": round(spmv_gbs, 1), "peak": PEAK_HBM_GBS,
+                     "path": "launch per phase (the step after the timed ones)",
                      "unit": "GB/s", "frac": round(spmv_gbs / PEAK_HBM_GBS, 4), "traffic": traffic,
                      "kernel": spmv_kernel,
                      "bytes_per_launch": spmv_bytes, "avg_us": round(spmv_avg_us, 2),

@@ -405,7 +405,10 @@ int hns_operator_assembly(const hns_operator *op);
  *                  of three per iteration; the same recurrence and stopping
  *                  rule, dot products summed over 1024 threads instead of
  *                  per-block partials; up to 4096 rows the vectors stay in
- *                  registers and LDS for the whole chunk).  The workgroup
+ *                  registers and LDS for the whole chunk; FP64 solves of up
+ *                  to 2560 rows with at most seven upper diagonals run whole
+ *                  in one launch of 512 threads: statistics, residuals,
+ *                  restarts and normalisation too).  The workgroup
  *                  stops by itself at the tolerance, so its chunks take up
  *                  to max(check_every, 1024) iterations (per-slot sessions:
  *                  the iterations of an advance).  Default 4096, 0 = never,

@@ -9,7 +9,9 @@
 // registers (a thread keeps the diagonal and both triangles of its rows; eight
 // wavefronts, so that 256 registers are there for it), p lives in LDS with
 // zeros around it, a row's fifteen reads of p are issued while the row before
-// is summed, and a sum over the workgroup costs one barrier.
+// is summed, and a sum over the workgroup costs one barrier.  Measured: the box
+// 437 -> 157 us; an iteration 1.7 us up to 1,536 rows (3.1 to 4.3 before), 3.4
+// against 4.7 at 2,048 and 7.1 against 8.1 at 2,560, the largest taken.
 //
 // Solves that the caller advances by a number of iterations (batch sessions)
 // keep r and p in their workspace and the rest in SmallState between launches:

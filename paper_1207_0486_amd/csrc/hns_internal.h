@@ -56,6 +56,10 @@ struct HostCSR {
 // workgroups where the product is latency-bound), two at and above it
 constexpr int64_t kOneRowMax = 250000;
 
+// Absent coupling in the diagonal arrays of the divergence forms (a bit pattern:
+// a coupling that is there and exactly zero is stored as +0)
+constexpr double kNoCoupling = -0.0;
+
 // Tiling of the one-launch CG chunks (cg_grid.hip): G workgroups (0: none
 // fits), each A planes by S places of the rows seen as planes of P
 constexpr int kGridBlock = 512;             // threads of a workgroup
@@ -204,7 +208,8 @@ struct hns_operator {
     // auxiliary forms for the step right-hand sides
     // (the divergence forms in diagonal arrays Bdia where M takes diagonal
     // storage: per component the diagonal, then for each offset o of M
-    // B(i, i + o), then B(i + o, i), n doubles each; else B and Bt in CSR)
+    // B(i, i + o), then B(i + o, i), n doubles each, kNoCoupling where the pair
+    // shares no tetrahedron; else B and Bt in CSR)
     hns::DevMatrix M, B[3], Bt[3], Ms;
     double *Bdia = nullptr;
     bool has_aux = false;

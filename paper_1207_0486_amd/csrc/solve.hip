@@ -1410,7 +1410,7 @@ static hns_status assemble_step_aux(hns_operator *op, const hns_mesh *mesh, cons
         HostCSR B, Bt;
         HNS_TRY(assemble_divergence_host(mesh, A, c, B));
         if (m > 0) {   // the pattern of A, whose offsets are M's
-            std::vector<double> dia((2 * (size_t)m + 1) * n, 0.0);
+            std::vector<double> dia((2 * (size_t)m + 1) * n, kNoCoupling);
             for (int64_t i = 0; i < n; ++i)
                 for (int32_t t = B.rowptr[i]; t < B.rowptr[i + 1]; ++t) {
                     const int64_t o = B.col[t] - i, row = o < 0 ? i + o : i;
@@ -1420,7 +1420,8 @@ static hns_status assemble_step_aux(hns_operator *op, const hns_mesh *mesh, cons
                         set_error("a divergence entry lies outside the mass matrix's diagonals");
                         return HNS_ERR_INVALID;
                     }
-                    dia[(o == 0 ? 0 : o > 0 ? 1 + k : 1 + m + k) * (size_t)n + row] = B.val[t];
+                    dia[(o == 0 ? 0 : o > 0 ? 1 + k : 1 + m + k) * (size_t)n + row] =
+                        B.val[t] == 0.0 ? 0.0 : B.val[t];   // -0 is kNoCoupling
                 }
             HNS_TRY_HIP(hipMemcpy(op->Bdia + c * (2 * (size_t)m + 1) * n, dia.data(),
                                   dia.size() * sizeof(double), hipMemcpyHostToDevice));

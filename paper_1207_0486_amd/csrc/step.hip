@@ -202,8 +202,10 @@ __global__ __launch_bounds__(kBlock) void k_copy_masked(int64_t n, double *__res
 // per row and component against 12 per entry of compressed rows, and what a
 // separate product, scaling and addition wrote and read again stays in
 // registers.  Bound by memory: the 45 arrays of B are 3/4 of the bytes.
-// An absent coupling is a stored 0 and takes no part (a non-finite value
-// at an unconnected node stays where it is).
+// An absent coupling takes no part (a non-finite value at an unconnected node
+// stays where it is): in M it is a stored 0, where a present one is positive; in
+// B, whose present couplings may be exactly 0 (two tetrahedra cancel on uniform
+// meshes), it is kNoCoupling, and a present 0 is multiplied like any other.
 // ---------------------------------------------------------------------------
 struct FormOffsets {
     int32_t o[kMaxDiag];
@@ -219,6 +221,12 @@ struct FormArgs {
 };
 
 __device__ __forceinline__ double times(double a, double x) { return a != 0.0 ? a * x : 0.0; }
+
+// the same for an entry of B
+__device__ __forceinline__ double div_times(double a, double x)
+{
+    return __double_as_longlong(a) != __double_as_longlong(kNoCoupling) ? a * x : 0.0;
+}
 
 // (M v_c)(i) for the NC vectors v + c n
 template <int NC>
@@ -248,7 +256,7 @@ __device__ __forceinline__ void div_row(const FormArgs &f, int64_t i, const doub
     const int m = f.m;
     const int64_t n = f.n, per = (int64_t)(2 * m + 1) * n;
 #pragma unroll
-    for (int c = 0; c < 3; ++c) acc[c] = times(f.B[c * per + i], x[(SAME ? 0 : c * n) + i]);
+    for (int c = 0; c < 3; ++c) acc[c] = div_times(f.B[c * per + i], x[(SAME ? 0 : c * n) + i]);
 #pragma unroll 2
     for (int k = 0; k < m; ++k) {
         const int64_t o = f.offs.o[k], iu = i + o < n ? i + o : n - 1, il = i >= o ? i - o : 0;
@@ -256,10 +264,10 @@ __device__ __forceinline__ void div_row(const FormArgs &f, int64_t i, const doub
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             const double *Bc = f.B + c * per;
-            const double au = i + o < n ? Bc[ku * n + i] : 0.0;
-            const double al = i >= o ? Bc[kl * n + il] : 0.0;
+            const double au = i + o < n ? Bc[ku * n + i] : kNoCoupling;
+            const double al = i >= o ? Bc[kl * n + il] : kNoCoupling;
             const double *xc = x + (SAME ? 0 : c * n);
-            acc[c] += times(au, xc[iu]) + times(al, xc[il]);
+            acc[c] += div_times(au, xc[iu]) + div_times(al, xc[il]);
         }
     }
 }
@@ -385,13 +393,13 @@ __global__ __launch_bounds__(kBlock) void k_div_apply(FormArgs f, const double *
     const int64_t n = f.n;
     GRID_STRIDE(i, n)
     {
-        double s = times(f.B[i], x[i]);
+        double s = div_times(f.B[i], x[i]);
         for (int k = 0; k < f.m; ++k) {
             const int64_t o = f.offs.o[k];
             const double *U = f.B + (TR ? 1 + f.m + k : 1 + k) * n;
             const double *L = f.B + (TR ? 1 + k : 1 + f.m + k) * n;
-            if (i + o < n) s += times(U[i], x[i + o]);
-            if (i >= o) s += times(L[i - o], x[i - o]);
+            if (i + o < n) s += div_times(U[i], x[i + o]);
+            if (i >= o) s += div_times(L[i - o], x[i - o]);
         }
         y[i] = s;
     }

@@ -1,0 +1,62 @@
+"""Edges of the step's forms in diagonal storage: non-finite values reach exactly
+the nodes they are coupled to, vectors that overlap, calls that run together."""
+import numpy as np
+import pytest
+
+import basin
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+NU = (1e3, 1e-2)
+DT = 3600.0
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1207_0486_amd import hns  # noqa: F401
+    return torch.device("cuda", 0)
+
+
+def _operator(m):
+    from paper_1207_0486_amd.hns import Operator
+    return Operator(m, *NU, DT, kind="helmholtz", step_aux=True)
+
+
+# a uniform box, where a tenth of the couplings of B are exactly 0 (half of its
+# diagonal among them), and a mesh with a bumpy floor
+MESHES = {"box": lambda: basin.box_mesh(6, 5, 4), "basin": lambda: basin.basin_mesh(7, 5, 4, seed=2)}
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("mesh", MESHES)
+def test_non_finite_values_reach_the_coupled_nodes(dev, mesh, value):
+    """0 times a non-finite value is NaN, so every node that shares a
+    tetrahedron with the value's node is non-finite, and no other node is."""
+    m = MESHES[mesh]()
+    op = _operator(m)
+    at = m.n // 2 + 1
+    near = np.zeros(m.n, dtype=bool)
+    near[m.tets[(m.tets == at).any(axis=1)].ravel()] = True
+    x = torch.ones(m.n, dtype=torch.float64, device=dev)
+    x[at] = value
+
+    def spread(y):
+        return ~torch.isfinite(y).cpu().numpy()
+
+    for name in ("B1", "B2", "B3", "B1T", "B2T", "B3T"):
+        assert np.array_equal(spread(op.apply_aux(name, x)), near), name
+    one = torch.ones(3, m.n, dtype=torch.float64, device=dev)
+    for c in range(3):
+        ut = one.clone()
+        ut[c] = x
+        assert np.array_equal(spread(op.step_pressure_rhs(ut)), near)
+    free = [((m.bc >> c) & 1) == 0 for c in range(3)]
+    for y in (op.step_correct(one, x), op.step_correct_rhs(7.0, one, x),
+              op.step_velocity_rhs(one, x)):
+        for c in range(3):
+            assert np.array_equal(spread(y[c]), near & free[c]), c
+    op.close()

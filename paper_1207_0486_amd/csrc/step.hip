@@ -422,6 +422,13 @@ bool overlaps(const double *a, int64_t na, const double *b, int64_t nb)
     return a && b && a < b + nb && b < a + na;
 }
 
+// The corrections add q to p before they read u~ and write the result; in one
+// launch that order holds only where p shares memory with none of them
+bool p_alone(int64_t n, const double *p, const double *q, const double *ut, const double *out)
+{
+    return !overlaps(p, n, q, n) && !overlaps(p, n, ut, 3 * n) && !overlaps(p, n, out, 3 * n);
+}
+
 hns_status check(const char *what)
 {
     hipError_t e = hipGetLastError();
@@ -526,7 +533,7 @@ hns_status hns_step_correct(hns_operator *op, const double *ut_dev, const double
     }
     hipStream_t s = (hipStream_t)stream;
     if (op->Bdia && !overlaps(q_dev, op->n, u_dev, 3 * op->n) &&
-        !overlaps(p_dev, op->n, q_dev, op->n)) {
+        p_alone(op->n, p_dev, q_dev, ut_dev, u_dev)) {
         const FormArgs f = form_args(op);
         k_correct<<<form_grid(f.n), kBlock, 0, s>>>(f, op->dt, ut_dev, q_dev, p_dev, op->lumped, u_dev);
         HNS_TRY(check("correction"));
@@ -690,7 +697,8 @@ hns_status hns_step_correct_rhs(hns_operator *op, double tau, const double *ut_d
     }
     hipStream_t s = (hipStream_t)stream;
     if (op->Bdia && !overlaps(rhs_dev, 3 * op->n, ut_dev, 3 * op->n) &&
-        !overlaps(rhs_dev, 3 * op->n, q_dev, op->n) && !overlaps(p_dev, op->n, q_dev, op->n)) {
+        !overlaps(rhs_dev, 3 * op->n, q_dev, op->n) &&
+        p_alone(op->n, p_dev, q_dev, ut_dev, rhs_dev)) {
         const FormArgs f = form_args(op);
         k_correct_rhs<<<form_grid(f.n), kBlock, 0, s>>>(f, tau, ut_dev, q_dev, p_dev, rhs_dev);
         HNS_TRY(check("correction right-hand side"));

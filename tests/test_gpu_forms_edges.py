@@ -60,3 +60,29 @@ def test_non_finite_values_reach_the_coupled_nodes(dev, mesh, value):
         for c in range(3):
             assert np.array_equal(spread(y[c]), near & free[c]), c
     op.close()
+
+
+@pytest.mark.parametrize("shift", [0, 1, 5])
+def test_pressure_inside_the_velocity(dev, shift):
+    """p += q comes first, also where p lies in u~ (then the forms read the
+    updated u~) or in the result (then the result replaces it)."""
+    m = basin.basin_mesh(19, 23, 6, seed=2)
+    op = _operator(m)
+    n = m.n
+    rng = np.random.default_rng(3)
+    ut = torch.as_tensor(rng.standard_normal((3, n)), device=dev)
+    q = torch.as_tensor(rng.standard_normal(n), device=dev)
+    for name, args in (("step_correct", ()), ("step_correct_rhs", (7.0,))):
+        call = getattr(op, name)
+        a, b = ut.clone(), ut.clone()
+        b.view(-1)[n + shift:2 * n + shift] += q
+        got = call(*args, a, q, a.view(-1)[n + shift:2 * n + shift])
+        assert torch.equal(a, b)
+        want = call(*args, b, q)
+        # the launches sum a row's entries in another order than the one pass
+        assert float((got - want).abs().max()) <= 1e-13 * float(want.abs().max())
+        out = torch.zeros_like(ut)
+        call(*args, ut, q, out.view(-1)[n + shift:2 * n + shift], out=out)
+        want = call(*args, ut, q)
+        assert float((out - want).abs().max()) <= 1e-13 * float(want.abs().max())
+    op.close()

@@ -504,9 +504,10 @@ hns_status hns_apply(hns_operator *op, int mask_bit, const double *x_dev, double
  * component c uses Dirichlet bit c-1 of mesh.bc.  All pointers are device.
  * The time step is the operator's dt (the implicit-Euler form of the
  * prediction step; a BDF2 step assembles with dt' = 2 dt / 3).
- * These calls use scratch memory of the operator: calls on one operator must
- * not overlap (different operators may run concurrently).  They return after
- * their work on `stream` has completed.
+ * These calls use scratch memory of the operator: those made on one operator at
+ * the same time (from several threads, a stream each) take turns; different
+ * operators run concurrently.  They return after their work on `stream` has
+ * completed.
  * ------------------------------------------------------------------------ */
 
 /* Velocity-prediction right-hand sides (eq. fofa_velo_pred_h multiplied by

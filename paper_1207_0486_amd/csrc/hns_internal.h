@@ -214,6 +214,7 @@ struct hns_operator {
     double *Bdia = nullptr;
     bool has_aux = false;
     double *step_tmp = nullptr;   // 3 n doubles of scratch for the step kernels
+    std::mutex step_mutex;        // held by a call while its kernels use step_tmp
     // mesh on the device for the advection term (HNS_STEP_AUX): coordinates
     // (n x 3), tetrahedra (ntet x 4) and the node -> tetrahedron incidence
     int64_t ntet = 0;

@@ -542,6 +542,7 @@ hns_status hns_step_correct(hns_operator *op, const double *ut_dev, const double
     }
     const int64_t n = op->n;
     const int G = stream_grid(n);
+    std::lock_guard<std::mutex> scratch(op->step_mutex);
     double *t0 = op->step_tmp;
     if (p_dev) {
         k_axpy<<<G, kBlock, 0, s>>>(n, p_dev, 1.0, q_dev);
@@ -566,6 +567,7 @@ hns_status hns_step_advection(hns_operator *op, const double *u_dev, double *out
         return HNS_ERR_INVALID;
     }
     hipStream_t s = (hipStream_t)stream;
+    std::lock_guard<std::mutex> scratch(op->step_mutex);
     k_interleave<<<stream_grid(op->n), kBlock, 0, s>>>(op->n, u_dev, op->step_tmp);
     HNS_TRY(check("advection"));
     k_advection<<<form_grid(op->n * kAdvLanes), kBlock, 0, s>>>(
@@ -598,6 +600,7 @@ static hns_status velocity_rhs(hns_operator *op, double tau, double a1, const do
 {
     const int64_t n = op->n;
     const int G = stream_grid(n);
+    std::lock_guard<std::mutex> scratch(op->step_mutex);
     if (op->Bdia && !overlaps(b_dev, 3 * n, p_dev, n) && !overlaps(b_dev, 3 * n, theta_dev, 2 * n)) {
         const FormArgs f = form_args(op);
         double *v = op->step_tmp;
@@ -673,6 +676,7 @@ static hns_status pressure_rhs(hns_operator *op, double scale, const double *ut_
         HNS_TRY_HIP(hipStreamSynchronize(s));
         return HNS_OK;
     }
+    std::lock_guard<std::mutex> scratch(op->step_mutex);
     double *t0 = op->step_tmp;
     for (int c = 0; c < 3; ++c) {
         HNS_TRY(apply_div(op, c, false, ut_dev + c * n, t0, s));
@@ -707,6 +711,7 @@ hns_status hns_step_correct_rhs(hns_operator *op, double tau, const double *ut_d
     }
     const int64_t n = op->n;
     const int G = stream_grid(n);
+    std::lock_guard<std::mutex> scratch(op->step_mutex);
     double *t0 = op->step_tmp, *t1 = op->step_tmp + n;
     if (p_dev) {
         k_axpy<<<G, kBlock, 0, s>>>(n, p_dev, 1.0, q_dev);

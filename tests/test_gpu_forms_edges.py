@@ -86,3 +86,39 @@ def test_pressure_inside_the_velocity(dev, shift):
         want = call(*args, ut, q)
         assert float((out - want).abs().max()) <= 1e-13 * float(want.abs().max())
     op.close()
+
+
+def test_calls_that_run_together(dev):
+    """Threads with a stream each call the forms of one operator at the same
+    time: every result is the one of the call alone, bit for bit."""
+    import threading
+    m = basin.basin_mesh(64, 60, 10, seed=2)
+    op = _operator(m)
+    rng = np.random.default_rng(3)
+    us = [torch.as_tensor(rng.standard_normal((3, m.n)), device=dev) for _ in range(4)]
+
+    def forms(k, stream=None):
+        adv = op.step_advection(us[k], stream=stream)
+        return adv, op.step_velocity_rhs_bdf(7.0, 1.0, us[k], adv=adv, stream=stream)
+
+    want = [forms(k) for k in range(4)]
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(k):
+        torch.cuda.set_device(dev)
+        s = torch.cuda.Stream(dev)
+        with torch.cuda.stream(s):
+            for _ in range(30):
+                got = forms(k, s)
+                s.synchronize()
+                if not all(torch.equal(a, b) for a, b in zip(got, want[k])):
+                    wrong.append(k)
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
+    op.close()

@@ -486,6 +486,20 @@ int hns_operator_assembly(const hns_operator *op);
  *                  non-positive pivot. */
 hns_status hns_set_param(hns_operator *op, const char *name, double value);
 
+/* What "one_launch" does on this operator: the tiling of its chunks in FP64
+ * (fp32 = 0) or FP32 (fp32 = 1), found when the first point-Jacobi solve builds
+ * the Jacobi-scaled operator (zeros before, and where none fits), and counts
+ * since the operator was assembled. */
+typedef struct {
+    int32_t workgroups;       /* of a chunk                                          */
+    int32_t rows_per_thread;  /* of the compiled form in use                         */
+    int32_t lds_bytes;        /* dynamic LDS of a workgroup                          */
+    int32_t reserved;
+    int64_t chunks;           /* chunks run to their end                             */
+    int64_t missed;           /* chunks whose workgroups gave up waiting             */
+} hns_one_launch_info;
+hns_status hns_one_launch_read(hns_operator *op, int fp32, hns_one_launch_info *info);
+
 /* y = A x on the device (FP64), with the rows of Dirichlet set mask_bit
  * zeroed and its columns ignored (mask_bit = -1: plain product). */
 hns_status hns_apply(hns_operator *op, int mask_bit, const double *x_dev, double *y_dev,

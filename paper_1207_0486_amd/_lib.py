@@ -50,6 +50,12 @@ class hns_solve_info(C.Structure):
                 ("status", C.c_int32), ("reserved", C.c_int32)]
 
 
+class hns_one_launch_info(C.Structure):
+    _fields_ = [("workgroups", C.c_int32), ("rows_per_thread", C.c_int32),
+                ("lds_bytes", C.c_int32), ("reserved", C.c_int32),
+                ("chunks", C.c_int64), ("missed", C.c_int64)]
+
+
 # every exported function with its argument and result types
 _SIGNATURES = {
     "hns_assemble": (C.c_int, [C.POINTER(hns_mesh), C.c_double, C.c_double, C.c_double,
@@ -87,6 +93,7 @@ _SIGNATURES = {
     "hns_operator_line_len": (C.c_int, [C.c_void_p]),
     "hns_operator_assembly": (C.c_int, [C.c_void_p]),
     "hns_set_param": (C.c_int, [C.c_void_p, C.c_char_p, C.c_double]),
+    "hns_one_launch_read": (C.c_int, [C.c_void_p, C.c_int, C.POINTER(hns_one_launch_info)]),
     "hns_apply": (C.c_int, [C.c_void_p, C.c_int, C.c_void_p, C.c_void_p, C.c_void_p]),
     "hns_step_velocity_rhs": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p,
                                         C.c_void_p, C.c_void_p, C.c_void_p]),

@@ -664,6 +664,7 @@ bool plan_for(const DevMatrix &S, int cus, GridPlan &best)
                 p.nch = (int)nch;
                 p.H = (int)H;
                 p.instance = i;
+                p.rpt = inst[i].rpt;
                 for (int k = 0; k < m; ++k)
                     p.dl[k] = k < split ? S.off[k] : (int)(pitch + S.off[k] - P);
                 best = p;

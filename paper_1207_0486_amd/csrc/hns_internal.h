@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <array>
+#include <atomic>
 #include <cstdint>
 #include <mutex>
 #include <string>
@@ -69,7 +70,7 @@ constexpr int kMeetPolls = 1 << 21;         // bound of a wait between them (abo
 constexpr int kGridDiag = 7;                // upper diagonals the kernel is compiled for
 struct GridPlan {
     int G = 0, P = 0, planes = 0, A = 0, S = 0, nS = 0, nch = 0, H = 0, pitch = 0, hcap = 0;
-    int instance = 0;
+    int instance = 0, rpt = 0;   // the compiled form, and its rows per thread
     int wlds = 0;
     size_t lds = 0;
     double cost = 0;             // estimated us per iteration
@@ -272,6 +273,8 @@ struct hns_operator {
     // plan fits and fuse_dir is automatic, 0 never
     int one_launch = -1;
     int meet_polls = hns::kMeetPolls;   // polls before a one-launch chunk gives up
+    // its chunks run to their end and those given up, in FP64 and FP32
+    std::atomic<int64_t> grid_chunks[2] = {}, grid_missed[2] = {};
     // batch sessions: 0 per-slot recurrences up to 2 slots, the shared
     // multi-right-hand-side block above; 1 always the block; 2 always per slot
     int session_mode = 0;

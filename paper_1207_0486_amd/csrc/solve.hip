@@ -507,6 +507,7 @@ struct ChunkedSolve {
     double tol2 = 0, drop2 = 0, rr_true = 0, bb = 0, rr_prev = 0, rr_best = INFINITY;
     const void *dinv = nullptr;
     bool whole = false;          // one workgroup runs everything (launch_small_solve)
+    bool grid = false;           // the chunk under way is a one-launch chunk
 
     int which() const { return mixed ? 1 : 0; }
 
@@ -691,7 +692,9 @@ struct ChunkedSolve {
                         : grid_wanted(op, w, p, c.scaled) ? std::max(op->check_every, kGridChunk)
                                                           : op->check_every;
         const int chunk = std::min({c.max_iter - hr.iter, per, budget});
+        grid = false;
         if (chunk > 0 && hr.stop == 0) {
+            grid = grid_wanted(op, w, p, c.scaled);
             void *x = mixed ? (void *)w->d32 : c.scaled ? (void *)w->z : (void *)c.x;
             void *r = mixed ? (void *)w->r32 : (void *)w->r;
             void *pp = mixed ? (void *)w->p32 : (void *)w->p;
@@ -713,6 +716,7 @@ struct ChunkedSolve {
         if (whole) return whole_read();
         Scalars &h = w->host[0];
         Scalars &hr = w->host[which()];
+        if (grid) ++(hr.lost ? op->grid_missed : op->grid_chunks)[mixed];
         if (hr.lost) {   // void vectors: again from x, with a launch per phase
             w->no_grid = true;
             HNS_TRY(true_residual_fp64(c));
@@ -1763,6 +1767,27 @@ hns_status hns_set_param(hns_operator *op, const char *name, double value)
         set_error("unknown parameter or bad value: %s = %g", name, value);
         return HNS_ERR_INVALID;
     }
+    return HNS_OK;
+}
+
+hns_status hns_one_launch_read(hns_operator *op, int fp32, hns_one_launch_info *info)
+{
+    if (!op || !info || (fp32 != 0 && fp32 != 1)) {
+        set_error("hns_one_launch_read: bad arguments");
+        return HNS_ERR_INVALID;
+    }
+    memset(info, 0, sizeof(*info));
+    {
+        std::lock_guard<std::mutex> g(op->line_mutex);
+        const GridPlan &p = fp32 ? op->S.grid32 : op->S.grid64;
+        if (p.G > 0) {
+            info->workgroups = p.G;
+            info->rows_per_thread = p.rpt;
+            info->lds_bytes = (int32_t)p.lds;
+        }
+    }
+    info->chunks = op->grid_chunks[fp32];
+    info->missed = op->grid_missed[fp32];
     return HNS_OK;
 }
 

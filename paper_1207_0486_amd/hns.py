@@ -176,6 +176,16 @@ class Operator:
         if st != L.HNS_OK:
             raise HNSError(st, "hns_set_param")
 
+    def one_launch_info(self, mode: str = "fp64") -> dict:
+        """Tiling and counts of the one-launch CG chunks (see "one_launch") in FP64
+        ("fp64") or FP32 ("mixed"): workgroups (0: none), rows_per_thread,
+        lds_bytes, chunks, missed."""
+        info = L.hns_one_launch_info()
+        st = L.lib().hns_one_launch_read(self._h, int(mode == "mixed"), C.byref(info))
+        if st != L.HNS_OK:
+            raise HNSError(st, "hns_one_launch_read")
+        return {k: int(getattr(info, k)) for k, _ in info._fields_ if k != "reserved"}
+
     def profile(self, period: int = 1):
         """Time every `period`-th CG iteration with HIP events (0 = off)."""
         st = L.lib().hns_profile_enable(self._h, int(period))

@@ -1,0 +1,105 @@
+"""Which compiled form of the one-launch CG chunks (csrc/cg_grid.hip) runs, asked of
+the library, and that it ran: every form against the launch-per-phase iterations,
+and the states a solve can find its chunks in."""
+import numpy as np
+import pytest
+
+import basin
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+NU = (1e3, 1e-2)
+DT = 3600.0
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1207_0486_amd import hns  # noqa: F401
+    return torch.device("cuda", 0)
+
+
+def _operator(m, bit, keep_fp32=False):
+    from paper_1207_0486_amd.hns import Operator
+    op = Operator(m, NU[0], NU[1], DT, kind="poisson" if bit < 0 else "helmholtz",
+                  keep_fp32=keep_fp32, gpu_assembly=True)
+    op.set_param("small_n", 0)
+    return op
+
+
+def _rhs(m, bit, seed, dev):
+    d = None if bit < 0 else ((m.bc >> bit) & 1) == 1
+    b = basin.normal_rhs(m.n, seed, zero_mean=bit < 0, dirichlet=d)
+    return torch.as_tensor(b, device=dev)
+
+
+def _rel(x, y):
+    return float((x - y).norm() / y.norm())
+
+
+# rows per thread of the form that 256 CUs take, in FP64 and FP32
+FORMS = [((30, 28, 7), 1, 1), ((61, 47, 13), 2, 2), ((90, 80, 11), 4, 4), ((180, 190, 21), 6, 8),
+         ((240, 189, 17), 8, 8), ((237, 192, 18), 8, 8), ((250, 200, 22), 12, 12)]
+
+
+@pytest.mark.parametrize("grid, rows64, rows32", FORMS,
+                         ids=["x".join(map(str, g)) for g, _, _ in FORMS])
+def test_the_expected_form_runs_and_equals_the_launches(dev, grid, rows64, rows32):
+    """40 FP64 iterations equal those of a launch per phase to rounding (the dot
+    products' order differs); a mixed velocity solve meets its tolerance in the
+    same number of iterations."""
+    if torch.cuda.get_device_properties(dev).multi_processor_count != 256:
+        pytest.skip("tilings of 256 CUs")
+    m = basin.basin_mesh(*grid, seed=5)
+    b = _rhs(m, -1, 21, dev)
+    op = _operator(m, -1)
+    assert op.one_launch_info()["workgroups"] == 0          # nothing planned yet
+    xs = {}
+    for one in (0, -1):
+        op.set_param("one_launch", one)
+        xs[one], info = op.solve(b, tol=1e-12, max_iter=40, check=False)
+        assert info.iterations == 40
+        assert (op.one_launch_info()["chunks"] > 0) == (one == -1)
+    got = op.one_launch_info()
+    assert got["rows_per_thread"] == rows64 and got["missed"] == 0
+    op.close()
+    assert _rel(xs[-1], xs[0]) <= 1e-11
+    b = _rhs(m, 1, 22, dev)
+    op = _operator(m, 1, keep_fp32=True)
+    it = {}
+    for one in (0, -1):
+        op.set_param("one_launch", one)
+        x, info = op.solve(b, tol=1e-11, mask_bit=1, mode="mixed")
+        assert info.status == 0 and info.relres_true <= 1e-11
+        it[one] = info.iterations
+        assert (op.one_launch_info("mixed")["chunks"] > 0) == (one == -1)
+    got = op.one_launch_info("mixed")
+    assert got["rows_per_thread"] == rows32 and got["missed"] == 0
+    assert op.one_launch_info()["chunks"] == 0              # FP64 chunks: none in a mixed solve
+    op.close()
+    assert abs(it[-1] - it[0]) <= 1
+
+
+def test_a_missed_meeting_is_counted(dev):
+    m = basin.basin_mesh(40, 36, 6, seed=5)
+    for mode in ("fp64", "mixed"):
+        b = _rhs(m, 1, 41, dev)
+        op = _operator(m, 1, keep_fp32=True)
+        op.set_param("meet_polls", 0)
+        x, info = op.solve(b, tol=1e-10, mask_bit=1, mode=mode)
+        got = op.one_launch_info(mode)
+        op.close()
+        assert info.status == 0 and got["missed"] == 1 and got["chunks"] == 0
+
+
+def test_bad_queries_refused(dev):
+    import ctypes as C
+    from paper_1207_0486_amd import _lib as L
+    op = _operator(basin.box_mesh(4, 4, 2), -1)
+    info = L.hns_one_launch_info()
+    for args in ((None, 0, C.byref(info)), (op._h, 2, C.byref(info)), (op._h, 0, None)):
+        assert L.lib().hns_one_launch_read(*args) == L.HNS_ERR_INVALID
+    op.close()

@@ -723,13 +723,16 @@ hns_status launch_t(const IterArgs &a, const GridPlan &p, int parity, int count,
     return HNS_OK;
 }
 
+// The limit on an instance's dynamic LDS belongs to the process: it is set to the
+// most that any tiling takes, so that operators planned one after the other, or at
+// the same time, do not lower it below what another launches with.
 template <typename TX>
 bool ready(GridPlan &p)
 {
     int ni = 0, blocks = 0;
     const Instance<TX> *inst = instances(&ni, TX());
     const void *k = (const void *)inst[p.instance].k;
-    if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds) !=
+    if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax) !=
             hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k, kGT, p.lds) != hipSuccess) {
         (void)hipGetLastError();

@@ -103,3 +103,20 @@ def test_bad_queries_refused(dev):
     for args in ((None, 0, C.byref(info)), (op._h, 2, C.byref(info)), (op._h, 0, None)):
         assert L.lib().hns_one_launch_read(*args) == L.HNS_ERR_INVALID
     op.close()
+
+
+def test_operators_on_one_form(dev):
+    """Operators that share a compiled form (4 rows per thread) with unlike tiles:
+    the larger solves as before after a smaller one was planned."""
+    m, small = basin.basin_mesh(160, 140, 20, seed=5), basin.basin_mesh(90, 80, 11, seed=5)
+    b, bs = _rhs(m, 1, 51, dev), _rhs(small, 1, 52, dev)
+    op, other = _operator(m, 1), _operator(small, 1)
+    x, info = op.solve(b, tol=1e-10, mask_bit=1)
+    y, _ = other.solve(bs, tol=1e-10, mask_bit=1)
+    z, again = op.solve(b, tol=1e-10, mask_bit=1)
+    one, two = op.one_launch_info(), other.one_launch_info()
+    op.close()
+    other.close()
+    assert one["rows_per_thread"] == two["rows_per_thread"] == 4
+    assert one["lds_bytes"] > two["lds_bytes"] and one["chunks"] >= 2 and two["chunks"] >= 1
+    assert again.status == 0 and again.iterations == info.iterations and torch.equal(x, z)

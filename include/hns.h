@@ -441,15 +441,23 @@ int hns_operator_assembly(const hns_operator *op);
  *                  takes at most 4 MiB (524288 FP64 / 1048576 FP32 rows),
  *                  0 never, 1 always.  Per-kernel timing then times the
  *                  product (with the direction update) and the update.
- *   "one_launch"   the Jacobi-scaled recurrence above in one cooperative launch
- *                  per chunk of up to max(check_every, 1024) iterations, the
+ *   "one_launch"   the Jacobi-scaled recurrence above in one launch per chunk
+ *                  of up to max(check_every, 1024) iterations, the
  *                  vectors on chip and the workgroups meeting once per dot
  *                  product: the same recurrence and stopping rule, the dot
  *                  products summed in another order.  -1 (default) where a
  *                  tiling fits (7 upper diagonals; the rows of one tile's
  *                  vectors in LDS: up to about 1.5M rows) and "fuse_dir" is
  *                  -1, 0 never.  Not used while per-kernel timing is enabled.
- *                  Launches of concurrent solves on one GPU take turns.
+ *                  Chunks of concurrent solves run side by side where
+ *                  their workgroups fit the GPU's CUs together (one each),
+ *                  else they take turns of about 1 ms in the order they
+ *                  came; the iterates do not depend on it.  Tilings of more
+ *                  than 128 workgroups (from about 130,000 rows) run alone: a
+ *                  program with four or more mixed-precision solves of that
+ *                  size under way at all times completes 1.4 to 2 times as
+ *                  many with "one_launch" 0 (two: 1 to 1.3 times; one at a
+ *                  time: 0.6 times).
  *   "meet_polls"   bound of a wait between those workgroups, in polls of about
  *                  1 us (0 .. 2^21, default 2^21); a solve whose workgroups
  *                  give up goes on with a launch per phase, from the last

@@ -40,11 +40,18 @@
 // for bit.  Two buffers alternate (q and p, whose memory the chunk does not
 // use otherwise).
 //
-// Progress.  The launch is cooperative, so all workgroups are resident.  A
-// poll is bounded all the same: on running out, the workgroup raises
-// Scalars::lost and leaves, the others run out in turn, and the caller
-// repeats the segment with a launch per phase (x is written by the segment's
-// end only, so nothing is lost but time).
+// Progress.  The workgroups wait for each other, so all of a launch must become
+// resident.  One takes a CU (512 threads of 256 registers), and a launch of G is
+// dealt round-robin to the 8 XCDs and the 4 shader engines of each: at most
+// ceil(G / 32) to an engine.  The caller admits launches while the sum of these
+// counts is at most the CUs of an engine (GridTurn in solve.hip), so each finds its
+// CUs as soon as kernels that do not wait have left them.  (hipLaunchCooperativeKernel
+// would run one such launch at a time, whatever its size, and block the calling
+// thread until it ends: eight threads solving 41,664 rows each got 192 solves per
+// second that way, 370 with launches per phase.)  A poll is bounded all the same:
+// on running out, the workgroup raises Scalars::lost and leaves, the others run out
+// in turn, and the caller repeats the segment with a launch per phase (x is written
+// by the segment's end only, so nothing is lost but time).
 #include <algorithm>
 #include <cmath>
 
@@ -718,8 +725,7 @@ hns_status launch_t(const IterArgs &a, const GridPlan &p, int parity, int count,
     k_clear_slots<<<(words + kBlock - 1) / kBlock, kBlock, 0, s>>>(g.slots, words);
     HNS_TRY_HIP(hipGetLastError());
     void *args[] = {&g};
-    HNS_TRY_HIP(hipLaunchCooperativeKernel((const void *)inst[p.instance].k, dim3(p.G), dim3(kGT),
-                                           args, (unsigned)p.lds, s));
+    HNS_TRY_HIP(hipLaunchKernel((const void *)inst[p.instance].k, dim3(p.G), dim3(kGT), args, p.lds, s));
     return HNS_OK;
 }
 
@@ -749,17 +755,19 @@ void grid_plans(DevMatrix &S)
                   "the slots use the partial-sum buffer");
     static_assert(kGridSlots >= kGridMaxWg + kGridMaxWg / kGroup, "slots of the groups");
     S.grid64 = S.grid32 = GridPlan{};
-    int dev = 0, cus = 0, coop = 0;
+    int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess) {
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
         (void)hipGetLastError();
         return;
     }
-    if (!coop) return;
+    cus = cus / kGridEngines * kGridEngines;   // as many on every shader engine
+    if (cus == 0) return;
     if (!plan_for<double>(S, cus, S.grid64) || !ready<double>(S.grid64)) S.grid64 = GridPlan{};
     if (S.dia32 && (!plan_for<float>(S, cus, S.grid32) || !ready<float>(S.grid32)))
         S.grid32 = GridPlan{};
+    S.grid64.dev = S.grid32.dev = dev;
+    S.grid64.room = S.grid32.room = cus / kGridEngines;
 }
 
 hns_status launch_cg_grid(const IterArgs &a, int parity, int count, int polls, hipStream_t s)

@@ -68,13 +68,17 @@ constexpr int kGridMaxWg = 256;             // workgroups
 constexpr int kGridSlots = kGridMaxWg + 64; // their slots and those of their groups
 constexpr int kMeetPolls = 1 << 21;         // bound of a wait between them (about 2 s)
 constexpr int kGridDiag = 7;                // upper diagonals the kernel is compiled for
+constexpr int kGridEngines = 32;            // shader engines a launch is dealt to
 struct GridPlan {
+    int dev = 0, room = 0;       // device, and CUs of one of its shader engines
     int G = 0, P = 0, planes = 0, A = 0, S = 0, nS = 0, nch = 0, H = 0, pitch = 0, hcap = 0;
     int instance = 0, rpt = 0;   // the compiled form, and its rows per thread
     int wlds = 0;
     size_t lds = 0;
     double cost = 0;             // estimated us per iteration
     int32_t dl[kGridDiag] = {0};
+    // CUs of a shader engine its workgroups take, at most
+    int layers() const { return (G + kGridEngines - 1) / kGridEngines; }
 };
 
 struct DevMatrix {

@@ -129,12 +129,12 @@ constexpr int64_t kSmallMaxN = 1 << 20;
 hns_status launch_cg_small(const IterArgs &a, int parity, int count, hipStream_t s);
 
 // The tilings of the one-launch chunks for the scaled operator S (host work,
-// once per operator), and `count` iterations of Jacobi-scaled CG in one
-// cooperative launch: the recurrence, scalars and stopping rule of
-// launch_iteration, dot products summed by workgroup in another order.  On
-// return x, r and p are those after the chunk; a.q is scratch.  Needs the
-// plan of a.prec (G > 0).  polls: bound of each wait.  Sets Scalars::lost when the workgroups fail to
-// meet (x, r, p void).
+// once per operator), and `count` iterations of Jacobi-scaled CG in one launch:
+// the recurrence, scalars and stopping rule of launch_iteration, dot products
+// summed by workgroup in another order.  On return x, r and p are those after the
+// chunk; a.q is scratch.  Needs the plan of a.prec (G > 0) and a GridTurn of it
+// (solve.hip), held until the launch has ended.  polls: bound of each wait.  Sets
+// Scalars::lost when the workgroups fail to meet (x, r, p void).
 void grid_plans(DevMatrix &S);
 hns_status launch_cg_grid(const IterArgs &a, int parity, int count, int polls, hipStream_t s);
 

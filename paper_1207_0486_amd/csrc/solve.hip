@@ -1,7 +1,9 @@
 // Host drivers of the CG solves and the C ABI of hns.h.
 #include <algorithm>
+#include <chrono>
 #include <climits>
 #include <cmath>
+#include <condition_variable>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -299,9 +301,9 @@ static bool fuse_wanted(const hns_operator *op, bool fp32)
     return (size_t)op->n * (fp32 ? sizeof(float) : sizeof(double)) <= kFuseBytes;
 }
 
-// Chunks in one cooperative launch (cg_grid.hip): where the operator has a
-// plan for the precision, unless the caller asked for a form of the launches
-// per phase, times them, or a chunk of this solve gave up.
+// Chunks in one launch (cg_grid.hip): where the operator has a plan for the
+// precision, unless the caller asked for a form of the launches per phase, times
+// them, or a chunk of this solve gave up.
 constexpr int kGridChunk = 1024;
 
 static bool grid_wanted(const hns_operator *op, const Workspace *w, Prec prec, bool scaled)
@@ -310,6 +312,87 @@ static bool grid_wanted(const hns_operator *op, const Workspace *w, Prec prec, b
     if (!w->borrowed && op->profile > 0) return false;
     return prec == Prec::F32 ? op->S.grid32.G > 0 : prec == Prec::F64 && op->S.grid64.G > 0;
 }
+
+// Room on a device for one-launch chunks, whose workgroups wait for each other:
+// those under way together take at most the CUs of a shader engine (GridPlan::layers
+// of each), so that all of them are resident.  Turns are served in the order they
+// were asked for, so a chunk that needs the whole chip is not overtaken for ever.
+struct GridRoom {
+    std::mutex m;
+    std::condition_variable cv;
+    int used = 0;                   // CUs of a shader engine taken
+    uint64_t asked = 0, served = 0;
+    std::chrono::steady_clock::time_point shared{};   // when two solves last met here
+};
+static GridRoom &grid_room(int dev)
+{
+    constexpr int kDevices = 64;   // (further devices share the first ones' room)
+    // never destroyed: a thread may still wait for its turn when the process ends
+    static GridRoom *const rooms = new GridRoom[kDevices];
+    return rooms[dev % kDevices];
+}
+
+// A turn: from before the launch until the caller has waited for its stream.  The
+// chunks of one turn run on one stream, one after the other, with the same plan.
+class GridTurn {
+public:
+    explicit GridTurn(hipStream_t stream) : s(stream) {}
+    GridTurn(const GridTurn &) = delete;
+    GridTurn &operator=(const GridTurn &) = delete;
+    // an error between the launch and the wait: the launch ends first
+    ~GridTurn()
+    {
+        if (!room) return;
+        (void)hipStreamSynchronize(s);
+        give();
+    }
+
+    void take(const GridPlan &p)
+    {
+        if (room) return;
+        GridRoom &r = grid_room(p.dev);
+        std::unique_lock<std::mutex> lock(r.m);
+        const uint64_t mine = r.asked++;
+        const auto now = std::chrono::steady_clock::now();
+        if (r.used > 0 || mine != r.served) r.shared = now;
+        alone = now - r.shared > std::chrono::milliseconds(250);
+        layers = std::min(p.layers(), p.room);
+        r.cv.wait(lock, [&] { return mine == r.served && r.used + layers <= p.room; });
+        ++r.served;
+        r.used += layers;
+        room = &r;
+        r.cv.notify_all();   // the next may fit beside this one
+    }
+
+    void give()
+    {
+        if (!room) return;
+        {
+            std::lock_guard<std::mutex> lock(room->m);
+            room->used -= layers;
+        }
+        room->cv.notify_all();
+        room = nullptr;
+    }
+
+    // Iterations of a chunk: `most`, and about 1 ms where other solves have been
+    // under way within the last quarter of a second, which bounds how long one of
+    // them waits for the room.  A chunk's end and start cost some 40 us, so one solve
+    // by itself takes long ones; where a chunk ends does not change the arithmetic.
+    // Solves of 9,801 rows every 2 ms beside one of 1,387,029 rows that runs all the
+    // time: 1.8 ms each (p99 3.0) with turns of 1 ms, 4.0 (6.0) with 2 ms, 0.6 (0.6)
+    // with launches per phase; the large one 9.5, 11.5 and 11.6 solves per second.
+    int iterations(const GridPlan &p, int most) const
+    {
+        return alone ? most : std::max(1, std::min(most, (int)(1e3 / std::max(p.cost, 1.0))));
+    }
+
+private:
+    hipStream_t s;
+    GridRoom *room = nullptr;
+    int layers = 0;
+    bool alone = true;
+};
 
 static hns_status enqueue_iterations(hns_operator *op, Workspace *w, Prec prec, int bit, void *x,
                                      void *r, void *p, void *q, const void *dinv, Scalars *sc,
@@ -674,8 +757,10 @@ struct ChunkedSolve {
     }
 
     // At most `budget` (and `check_every`) iterations, then the read of the
-    // recurrence's scalars into the pinned mirror; nothing is waited for.
-    hns_status enqueue(int budget)
+    // recurrence's scalars into the pinned mirror; nothing is waited for but the
+    // turn of a one-launch chunk, which the caller gives back once it has waited
+    // for the stream.
+    hns_status enqueue(int budget, GridTurn &turn)
     {
         hns_operator *op = c.op;
         Workspace *w = c.w;
@@ -687,14 +772,19 @@ struct ChunkedSolve {
         const void *lf = p == Prec::F64   ? (const void *)c.lfac
                          : p == Prec::F32 ? (const void *)c.lfac32
                                           : nullptr;
-        const int per = small_chunks(op, w, p, lf, p == Prec::F64 ? c.ic : nullptr, c.scaled)
-                            ? std::max(op->check_every, kSmallChunk)
-                        : grid_wanted(op, w, p, c.scaled) ? std::max(op->check_every, kGridChunk)
-                                                          : op->check_every;
-        const int chunk = std::min({c.max_iter - hr.iter, per, budget});
-        grid = false;
-        if (chunk > 0 && hr.stop == 0) {
-            grid = grid_wanted(op, w, p, c.scaled);
+        const int left = hr.stop == 0 ? std::min(c.max_iter - hr.iter, budget) : 0;
+        grid = left > 0 && grid_wanted(op, w, p, c.scaled);
+        int per = small_chunks(op, w, p, lf, p == Prec::F64 ? c.ic : nullptr, c.scaled)
+                      ? std::max(op->check_every, kSmallChunk)
+                      : op->check_every;
+        if (grid) {
+            const GridPlan &plan = p == Prec::F32 ? op->S.grid32 : op->S.grid64;
+            turn.take(plan);
+            per = std::max(op->check_every, kGridChunk);
+            if (budget == INT_MAX) per = turn.iterations(plan, per);   // else the caller's
+        }
+        const int chunk = std::min(left, per);
+        if (chunk > 0) {
             void *x = mixed ? (void *)w->d32 : c.scaled ? (void *)w->z : (void *)c.x;
             void *r = mixed ? (void *)w->r32 : (void *)w->r;
             void *pp = mixed ? (void *)w->p32 : (void *)w->p;
@@ -855,8 +945,10 @@ static hns_status run_to_end(ChunkedSolve &cs)
 {
     HNS_TRY(cs.begin(kWholeIterations));
     while (!cs.finished) {
-        HNS_TRY(cs.enqueue(INT_MAX));
+        GridTurn turn(cs.c.s);
+        HNS_TRY(cs.enqueue(INT_MAX, turn));
         HNS_TRY_HIP(hipStreamSynchronize(cs.c.s));
+        turn.give();
         HNS_TRY(cs.after());
     }
     return cs.end();
@@ -1172,11 +1264,13 @@ hns_status slot_session_advance(SlotSession *ss, int iterations, hipStream_t s, 
             if (sl.state == 1) run.push_back(&sl);
         if (run.empty() || done >= iterations) break;
         const int budget = std::min(ss->op->check_every, iterations - done);
+        GridTurn turn(s);   // one for all slots: their chunks follow each other
         for (auto *sl : run) {
             sl->cs.c.s = s;
-            HNS_TRY(sl->cs.enqueue(budget));
+            HNS_TRY(sl->cs.enqueue(budget, turn));
         }
         HNS_TRY_HIP(hipStreamSynchronize(s));
+        turn.give();
         for (auto *sl : run) {
             HNS_TRY(sl->cs.after());
             if (sl->cs.finished) {

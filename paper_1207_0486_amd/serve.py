@@ -9,7 +9,8 @@ Poisson or Helmholtz) arrive at any time.  The server
     first served);
   * runs one batch session per resident operator, each on its own worker
     thread and device stream, so different operators' solves overlap on the
-    GPU;
+    GPU (one-launch chunks too large to run side by side take turns, a chunk
+    of `check_every` iterations each);
   * lets new requests join a session's free slots at every chunk boundary
     while the slots already running keep iterating (continuous batching), and
     hands each result back as soon as its own slot finishes;

@@ -120,3 +120,51 @@ def test_operators_on_one_form(dev):
     assert one["rows_per_thread"] == two["rows_per_thread"] == 4
     assert one["lds_bytes"] > two["lds_bytes"] and one["chunks"] >= 2 and two["chunks"] >= 1
     assert again.status == 0 and again.iterations == info.iterations and torch.equal(x, z)
+
+
+@pytest.mark.parametrize("mode", ["fp64", "mixed"])
+def test_solves_that_run_together(dev, mode):
+    """Threads with an operator and a stream each, whose chunks fit the GPU side by
+    side or take turns (51 to 255 workgroups), as solves and as sessions: every
+    answer is the one of the solve alone, bit for bit, and no meeting is missed."""
+    import threading
+    from paper_1207_0486_amd.hns import BatchSession
+    grids = [((24, 24, 8), -1), ((24, 24, 8), 1), ((61, 47, 13), -1), ((61, 47, 13), 0),
+             ((128, 64, 20), 1), ((128, 128, 16), 2), ((180, 190, 21), 0)]
+    cases = []
+    for k, (grid, bit) in enumerate(grids):
+        m = basin.basin_mesh(*grid, seed=5)
+        op = _operator(m, bit, keep_fp32=True)
+        b = _rhs(m, bit, 60 + k, dev)
+        x, info = op.solve(b, tol=1e-9, mask_bit=bit, mode=mode)
+        cases.append((op, bit, b, x, info))
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(k):
+        op, bit, b, want, winfo = cases[k]
+        torch.cuda.set_device(dev)
+        s = torch.cuda.Stream(dev)
+        with torch.cuda.stream(s):
+            sess = BatchSession(op, 2, mode)
+            for _ in range(4 if bit < 0 else 12):
+                x, info = op.solve(b, tol=1e-9, mask_bit=bit, mode=mode, stream=s)
+                sess.add([1], [bit], [b], [1e-9], [100000], stream=s)
+                while sess.advance(64, stream=s):
+                    pass
+                y, got = sess.take(1, stream=s)
+                s.synchronize()
+                if not (torch.equal(x, want) and torch.equal(y, want)
+                        and info.iterations == got.iterations == winfo.iterations):
+                    wrong.append(k)
+            sess.close()
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(len(cases))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    missed = [c[0].one_launch_info(mode)["missed"] for c in cases]
+    for c in cases:
+        c[0].close()
+    assert not wrong and not any(missed)

@@ -461,7 +461,8 @@ int hns_operator_assembly(const hns_operator *op);
  *   "meet_polls"   bound of a wait between those workgroups, in polls of about
  *                  1 us (0 .. 2^21, default 2^21); a solve whose workgroups
  *                  give up goes on with a launch per phase, from the last
- *                  true residual
+ *                  true residual (one whose launch the device refuses: from
+ *                  where it is)
  *   "session_mode" form of the batch sessions opened afterwards: 0 (default)
  *                  per-slot recurrences up to 2 slots, the shared block above;
  *                  1 always the shared block; 2 always per slot
@@ -505,6 +506,7 @@ typedef struct {
     int32_t reserved;
     int64_t chunks;           /* chunks run to their end                             */
     int64_t missed;           /* chunks whose workgroups gave up waiting             */
+    int64_t refused;          /* launches that the device did not take               */
 } hns_one_launch_info;
 hns_status hns_one_launch_read(hns_operator *op, int fp32, hns_one_launch_info *info);
 

@@ -683,7 +683,7 @@ bool plan_for(const DevMatrix &S, int cus, GridPlan &best)
 
 template <typename TX>
 hns_status launch_t(const IterArgs &a, const GridPlan &p, int parity, int count, int polls,
-                    hipStream_t s)
+                    bool *refused, hipStream_t s)
 {
     const DevMatrix &S = *a.A;
     int ni = 0;
@@ -725,7 +725,9 @@ hns_status launch_t(const IterArgs &a, const GridPlan &p, int parity, int count,
     k_clear_slots<<<(words + kBlock - 1) / kBlock, kBlock, 0, s>>>(g.slots, words);
     HNS_TRY_HIP(hipGetLastError());
     void *args[] = {&g};
-    HNS_TRY_HIP(hipLaunchKernel((const void *)inst[p.instance].k, dim3(p.G), dim3(kGT), args, p.lds, s));
+    *refused = hipLaunchKernel((const void *)inst[p.instance].k, dim3(p.G), dim3(kGT), args, p.lds,
+                               s) != hipSuccess;
+    if (*refused) (void)hipGetLastError();
     return HNS_OK;
 }
 
@@ -770,16 +772,18 @@ void grid_plans(DevMatrix &S)
     S.grid64.room = S.grid32.room = cus / kGridEngines;
 }
 
-hns_status launch_cg_grid(const IterArgs &a, int parity, int count, int polls, hipStream_t s)
+hns_status launch_cg_grid(const IterArgs &a, int parity, int count, int polls, bool *refused,
+                          hipStream_t s)
 {
+    *refused = false;
     if (count <= 0) return HNS_OK;
     const GridPlan &p = a.prec == Prec::F32 ? a.A->grid32 : a.A->grid64;
     if (p.G <= 0 || !a.wjac || (a.prec != Prec::F64 && a.prec != Prec::F32)) {
         set_error("launch_cg_grid: unsupported configuration");
         return HNS_ERR_INVALID;
     }
-    return a.prec == Prec::F64 ? launch_t<double>(a, p, parity, count, polls, s)
-                               : launch_t<float>(a, p, parity, count, polls, s);
+    return a.prec == Prec::F64 ? launch_t<double>(a, p, parity, count, polls, refused, s)
+                               : launch_t<float>(a, p, parity, count, polls, refused, s);
 }
 
 }  // namespace hns

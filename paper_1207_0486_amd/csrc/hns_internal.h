@@ -277,8 +277,8 @@ struct hns_operator {
     // plan fits and fuse_dir is automatic, 0 never
     int one_launch = -1;
     int meet_polls = hns::kMeetPolls;   // polls before a one-launch chunk gives up
-    // its chunks run to their end and those given up, in FP64 and FP32
-    std::atomic<int64_t> grid_chunks[2] = {}, grid_missed[2] = {};
+    // its chunks run to their end, given up and refused, in FP64 and FP32
+    std::atomic<int64_t> grid_chunks[2] = {}, grid_missed[2] = {}, grid_refused[2] = {};
     // batch sessions: 0 per-slot recurrences up to 2 slots, the shared
     // multi-right-hand-side block above; 1 always the block; 2 always per slot
     int session_mode = 0;

@@ -134,9 +134,11 @@ hns_status launch_cg_small(const IterArgs &a, int parity, int count, hipStream_t
 // summed by workgroup in another order.  On return x, r and p are those after the
 // chunk; a.q is scratch.  Needs the plan of a.prec (G > 0) and a GridTurn of it
 // (solve.hip), held until the launch has ended.  polls: bound of each wait.  Sets
-// Scalars::lost when the workgroups fail to meet (x, r, p void).
+// Scalars::lost when the workgroups fail to meet (x, r, p void).  *refused: the
+// device does not take the launch (the vectors are as they were).
 void grid_plans(DevMatrix &S);
-hns_status launch_cg_grid(const IterArgs &a, int parity, int count, int polls, hipStream_t s);
+hns_status launch_cg_grid(const IterArgs &a, int parity, int count, int polls, bool *refused,
+                          hipStream_t s);
 
 // A whole FP64 point-Jacobi solve of a small operator in one launch of one
 // workgroup, or `count` iterations of it (resume: continues from r, p and *st of

@@ -303,7 +303,7 @@ static bool fuse_wanted(const hns_operator *op, bool fp32)
 
 // Chunks in one launch (cg_grid.hip): where the operator has a plan for the
 // precision, unless the caller asked for a form of the launches per phase, times
-// them, or a chunk of this solve gave up.
+// them, or a chunk of this solve gave up or was refused.
 constexpr int kGridChunk = 1024;
 
 static bool grid_wanted(const hns_operator *op, const Workspace *w, Prec prec, bool scaled)
@@ -421,8 +421,15 @@ static hns_status enqueue_iterations(hns_operator *op, Workspace *w, Prec prec, 
     }
     // latency-bound sizes: the whole chunk in one workgroup
     if (small_chunks(op, w, prec, lfac, ic, scaled)) return launch_cg_small(a, parity0, count, s);
-    if (grid_wanted(op, w, prec, scaled))
-        return launch_cg_grid(a, parity0, count, op->meet_polls, s);
+    if (grid_wanted(op, w, prec, scaled)) {
+        bool refused = false;
+        HNS_TRY(launch_cg_grid(a, parity0, count, op->meet_polls, &refused, s));
+        if (!refused) return HNS_OK;
+        // the device does not take it: this solve goes on with launches per phase
+        w->no_grid = true;
+        ++op->grid_refused[prec == Prec::F32];
+        count = std::min(count, op->check_every);
+    }
     // sampled: the iteration in the middle of each period window, so a chunk's
     // first iteration (launched after the host's read of the previous chunk,
     // on an idle GPU) is never timed unless every iteration is
@@ -793,6 +800,7 @@ struct ChunkedSolve {
             HNS_TRY(enqueue_iterations(op, w, p, c.bit, x, r, pp, q, di, w->sc + which(), chunk,
                                        since, c.s, lf, p == Prec::F64 ? c.ic : nullptr,
                                        c.scaled));
+            grid = grid && !w->no_grid;   // the device took the launch
         }
         HNS_TRY_HIP(hipMemcpyAsync(&w->host[which()], w->sc + which(), sizeof(Scalars),
                                    hipMemcpyDeviceToHost, c.s));
@@ -1882,6 +1890,7 @@ hns_status hns_one_launch_read(hns_operator *op, int fp32, hns_one_launch_info *
     }
     info->chunks = op->grid_chunks[fp32];
     info->missed = op->grid_missed[fp32];
+    info->refused = op->grid_refused[fp32];
     return HNS_OK;
 }
 

@@ -168,3 +168,85 @@ def test_solves_that_run_together(dev, mode):
     for c in cases:
         c[0].close()
     assert not wrong and not any(missed)
+
+
+# A hipLaunchKernel in front of the runtime's that refuses the chunks (the only
+# launches of 512 threads in more than one workgroup) while a flag is set.
+REFUSE_C = """
+#include <stdint.h>
+#include <stddef.h>
+typedef struct { uint32_t x, y, z; } dim3;
+typedef int (*launch_t)(const void *, dim3, dim3, void **, size_t, void *);
+static launch_t real;
+static int refuse, refused;
+void set_real(void *f) { real = (launch_t)f; }
+void set_refuse(int on) { refuse = on; }
+int get_refused(void) { return refused; }
+int hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t lds, void *s)
+{
+    if (!real) return 1;
+    if (refuse && b.x == 512 && g.x > 1) { ++refused; return 701; }
+    return real(f, g, b, args, lds, s);
+}
+"""
+
+REFUSE_PY = """
+import ctypes, os, sys
+front = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)   # before the library that it stands in front of
+sys.path.insert(0, sys.argv[2])
+import torch   # loads the runtime; every launch below, torch's too, goes through the front
+hip = next(l.split()[-1] for l in open("/proc/self/maps") if "libamdhip64" in l)
+front.set_real.argtypes = [ctypes.c_void_p]
+front.set_real(ctypes.cast(ctypes.CDLL(hip).hipLaunchKernel, ctypes.c_void_p))
+import basin
+from paper_1207_0486_amd.hns import BatchSession, Operator
+dev = torch.device("cuda", 0)
+m = basin.basin_mesh(40, 36, 6, seed=5)
+d = ((m.bc >> 1) & 1) == 1
+b = torch.as_tensor(basin.normal_rhs(m.n, 41, dirichlet=d), device=dev)
+for mode in ("fp64", "mixed"):
+    op = Operator(m, 1e3, 1e-2, 3600.0, kind="helmholtz", keep_fp32=True, gpu_assembly=True)
+    op.set_param("small_n", 0)
+    op.set_param("check_every", 4)
+    op.set_param("one_launch", 0)
+    want, i = op.solve(b, tol=1e-10, mask_bit=1, mode=mode)
+    op.set_param("one_launch", -1)
+    front.set_refuse(1)
+    got, j = op.solve(b, tol=1e-10, mask_bit=1, mode=mode)
+    assert j.status == 0 and i.iterations == j.iterations and torch.equal(got, want), mode
+    info = op.one_launch_info(mode)
+    assert info["chunks"] == 0 and info["refused"] == 1, info
+    # refused in the middle: the rest of the iterations, from where it is
+    front.set_refuse(0)
+    s = BatchSession(op, 1, mode)
+    s.add([0], [1], [b], [1e-10], [1000])
+    s.advance(4)
+    front.set_refuse(1)
+    while s.advance(4):
+        pass
+    y, k = s.take(0)
+    info = op.one_launch_info(mode)
+    assert k.status == 0 and abs(k.iterations - i.iterations) <= 1 and info["chunks"] == 1, (k, info)
+    assert info["refused"] == 2, info
+    assert float((y - want).norm() / want.norm()) <= 1e-9
+    s.close()
+    front.set_refuse(0)
+    op.close()
+assert front.get_refused() == 4
+print("refused launches fell back")
+"""
+
+
+def test_a_refused_launch_falls_back(dev, tmp_path):
+    """The device refuses the chunk's launch: the solve takes the launches per
+    phase, to their bits, and so does the rest of one that has begun."""
+    import os
+    import subprocess
+    import sys
+    c, so = tmp_path / "refuse.c", tmp_path / "librefuse.so"
+    c.write_text(REFUSE_C)
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", str(so), str(c)], check=True)
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    out = subprocess.run([sys.executable, "-c", REFUSE_PY, str(so), root], capture_output=True,
+                         text=True, timeout=100, cwd=root)
+    assert out.returncode == 0 and "refused launches fell back" in out.stdout, out.stderr[-2000:]

@@ -461,8 +461,11 @@ int hns_operator_assembly(const hns_operator *op);
  *   "meet_polls"   bound of a wait between those workgroups, in polls of about
  *                  1 us (0 .. 2^21, default 2^21); a solve whose workgroups
  *                  give up goes on with a launch per phase, from the last
- *                  true residual (one whose launch the device refuses: from
- *                  where it is)
+ *                  true residual (the iterations since are not counted), and
+ *                  the operator's next 16 solves, twice as many after each
+ *                  further miss, take launches per phase from the start,
+ *                  until "one_launch" or "meet_polls" is set again (a solve
+ *                  whose launch the device refuses: from where it is)
  *   "session_mode" form of the batch sessions opened afterwards: 0 (default)
  *                  per-slot recurrences up to 2 slots, the shared block above;
  *                  1 always the shared block; 2 always per slot

@@ -277,6 +277,9 @@ struct hns_operator {
     // plan fits and fuse_dir is automatic, 0 never
     int one_launch = -1;
     int meet_polls = hns::kMeetPolls;   // polls before a one-launch chunk gives up
+    // solves still to go without them after a missed meeting, and how many the
+    // last one set
+    std::atomic<int> grid_resting{0}, grid_rest_next{0};
     // its chunks run to their end, given up and refused, in FP64 and FP32
     std::atomic<int64_t> grid_chunks[2] = {}, grid_missed[2] = {}, grid_refused[2] = {};
     // batch sessions: 0 per-slot recurrences up to 2 slots, the shared

@@ -313,6 +313,28 @@ static bool grid_wanted(const hns_operator *op, const Workspace *w, Prec prec, b
     return prec == Prec::F32 ? op->S.grid32.G > 0 : prec == Prec::F64 && op->S.grid64.G > 0;
 }
 
+// Workgroups that missed a meeting will miss the next one too where another
+// process holds their CUs: the operator's next solves (16, twice as many after each
+// further miss) take launches per phase at once instead of waiting out the bound
+// again.  A chunk that runs to its end, or a new setting, ends that.
+constexpr int kRestFirst = 16, kRestMost = 1 << 16;
+
+static void grid_rest(hns_operator *op)
+{
+    const int n = std::min(kRestMost, std::max(kRestFirst, 2 * op->grid_rest_next.load()));
+    op->grid_rest_next = n;
+    op->grid_resting = n;
+}
+
+static bool grid_resting(hns_operator *op)
+{
+    int n = op->grid_resting.load();
+    while (n > 0 && !op->grid_resting.compare_exchange_weak(n, n - 1)) {}
+    return n > 0;
+}
+
+static void grid_awake(hns_operator *op) { op->grid_resting = op->grid_rest_next = 0; }
+
 // Room on a device for one-launch chunks, whose workgroups wait for each other:
 // those under way together take at most the CUs of a shader engine (GridPlan::layers
 // of each), so that all of them are resident.  Turns are served in the order they
@@ -594,6 +616,7 @@ struct ChunkedSolve {
     hns_status status = HNS_NOT_CONVERGED;
     bool fresh = true;
     int since = 0, replacements = 0, stalls = 0, floor_checks = 0, before = 0;
+    int kept = 0;                // iterations whose work c.x holds
     double tol2 = 0, drop2 = 0, rr_true = 0, bb = 0, rr_prev = 0, rr_best = INFINITY;
     const void *dinv = nullptr;
     bool whole = false;          // one workgroup runs everything (launch_small_solve)
@@ -666,7 +689,7 @@ struct ChunkedSolve {
         hns_operator *op = c.op;
         Workspace *w = c.w;
         info->outer_iterations = 0;
-        w->no_grid = false;
+        w->no_grid = c.scaled && grid_resting(op);
         whole = !mixed && whole_wanted(c, prec);
         if (whole) {
             memset(&w->host[0], 0, sizeof(Scalars));
@@ -817,20 +840,22 @@ struct ChunkedSolve {
         if (grid) ++(hr.lost ? op->grid_missed : op->grid_chunks)[mixed];
         if (hr.lost) {   // void vectors: again from x, with a launch per phase
             w->no_grid = true;
+            grid_rest(op);
             HNS_TRY(true_residual_fp64(c));
             HNS_TRY(pull_scalars(w, 0, c.s));
             hr.lost = 0;
-            hr.iter = before;
-            info->iterations = before;
+            hr.iter = kept;   // those since x was last brought up to date are dropped
+            info->iterations = kept;
             fresh = true;
             return HNS_OK;
         }
+        if (grid) op->grid_rest_next = 0;
         since += hr.iter - before;
         HNS_TRY(account_iterations(op, w, mixed, hr.iter - before));
         if (hr.stop == 0 && hr.iter < c.max_iter) return HNS_OK;   // still running
         if (mixed) {
             Scalars &hi = w->host[1];
-            info->iterations = hi.iter;
+            info->iterations = kept = hi.iter;
             const bool broke = (hi.stop == 2);
             // collect the FP32 correction and recompute the true residual in FP64
             if (c.scaled)
@@ -876,7 +901,7 @@ struct ChunkedSolve {
         }
         const bool storage = (prec == Prec::F32Store);
         if (c.scaled) HNS_TRY(launch_scale_out(op->n, Prec::F64, c.x, w->z, op->jac_s, c.s));
-        info->iterations = h.iter;
+        info->iterations = kept = h.iter;
         if (h.stop == 2) {
             set_error("CG breakdown after %d iterations (p^T A p = %g)", h.iter, h.gamma);
             return done(HNS_ERR_BREAKDOWN);
@@ -1840,8 +1865,10 @@ hns_status hns_set_param(hns_operator *op, const char *name, double value)
         op->fuse_dir = (int)value;
     } else if (k == "one_launch" && (value == -1 || value == 0)) {
         op->one_launch = (int)value;
+        grid_awake(op);
     } else if (k == "meet_polls" && value >= 0 && value <= kMeetPolls && value == (int)value) {
         op->meet_polls = (int)value;
+        grid_awake(op);
     } else if (k == "session_mode" && (value == 0 || value == 1 || value == 2)) {
         op->session_mode = (int)value;
     } else if (k == "small_n" && value >= 0 && value <= (double)kSmallMaxN &&

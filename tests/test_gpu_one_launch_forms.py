@@ -250,3 +250,55 @@ def test_a_refused_launch_falls_back(dev, tmp_path):
     out = subprocess.run([sys.executable, "-c", REFUSE_PY, str(so), root], capture_output=True,
                          text=True, timeout=100, cwd=root)
     assert out.returncode == 0 and "refused launches fell back" in out.stdout, out.stderr[-2000:]
+
+
+@pytest.mark.parametrize("bit, mode", [(-1, "fp64"), (1, "fp64"), (-1, "mixed"), (1, "mixed")])
+def test_a_meeting_missed_later(dev, bit, mode):
+    """Chunks that run, then one whose workgroups give up: the iterations that x
+    does not hold are dropped and not counted.  FP64 starts again from the guess, to
+    the launches' bits; mixed precision from its last replacement."""
+    from paper_1207_0486_amd.hns import BatchSession
+    m = basin.basin_mesh(40, 36, 6, seed=5)
+    b = _rhs(m, bit, 71, dev)
+    op = _operator(m, bit, keep_fp32=True)
+    op.set_param("one_launch", 0)
+    want, winfo = op.solve(b, tol=1e-10, mask_bit=bit, mode=mode)
+    op.set_param("one_launch", -1)
+    s = BatchSession(op, 1, mode)
+    # (the cap: mixed solves restart their directions at the miss)
+    cap = winfo.iterations if mode == "fp64" else 2 * winfo.iterations
+    s.add([0], [bit], [b], [1e-10], [cap])
+    for n in (3, 5, 7):
+        assert s.advance(n) == 1
+    before = op.one_launch_info(mode)["chunks"]
+    op.set_param("meet_polls", 0)
+    while s.advance(1000):
+        pass
+    x, info = s.take(0)
+    s.close()
+    got = op.one_launch_info(mode)
+    assert before >= 3 and got["chunks"] == before and got["missed"] == 1
+    assert info.status == 0 and info.relres_true <= 1e-10 and info.iterations <= cap
+    if mode == "fp64":
+        assert info.iterations == winfo.iterations and torch.equal(x, want)
+    op.close()
+
+
+def test_a_missed_meeting_is_remembered(dev):
+    """The next 16 solves of the operator take launches per phase without trying
+    (32 after the next miss), until a setting asks for one launch again."""
+    m = basin.basin_mesh(40, 36, 6, seed=5)
+    b = _rhs(m, 1, 81, dev)
+    op = _operator(m, 1)
+    op.set_param("meet_polls", 0)
+    missed = []
+    for _ in range(60):
+        assert op.solve(b, tol=1e-6, mask_bit=1)[1].status == 0
+        missed.append(op.one_launch_info()["missed"])
+    assert missed == [1] * 17 + [2] * 33 + [3] * 10
+    assert op.one_launch_info()["chunks"] == 0
+    op.set_param("meet_polls", 1 << 21)
+    op.solve(b, tol=1e-6, mask_bit=1)
+    got = op.one_launch_info()
+    op.close()
+    assert got["chunks"] == 1 and got["missed"] == 3

@@ -616,12 +616,15 @@ size_t lds_bytes(const GridPlan &p, size_t vb, int rpt, int in_lds, bool wlds)
 // Time of one iteration of a plan in us, fitted to phases timed on MI355X: two
 // meetings; product, r and p updates per 512 rows of a workgroup (LDS latency
 // more than its rate: FP32 and FP64 alike); what is read from memory, at the
-// 5 TB/s such reads reached.
+// 8.7 TB/s such reads reached (they stay in the caches between iterations: 129 MB
+// at 256x256x20, 108 MB at 250x200x22).  Estimated / measured in FP64, us: 7.8 / 7.6
+// at 160x140x20, 10.0 / 9.6 at 200x180x20, 12.9 / 12.3 at 240x189x17, 22.6 / 22.7 at
+// 250x200x22, 25.7 / 25.5 at 256x256x20.
 double plan_cost(int G, int rpt, int streamed, bool xreg, int halo, size_t vb)
 {
     const double meet = G <= 64 ? 3.6 : G <= kFlat ? 4.6 : 5.4;
     const double mem = streamed * vb + (xreg ? 0.0 : 2.0 * vb);
-    return meet + 0.6 + 0.37 * rpt + G * kGT * (double)rpt * mem / 5e6 + 0.15 * halo / kGT;
+    return meet + 0.6 + 0.37 * rpt + G * kGT * (double)rpt * mem / 8.7e6 + 0.15 * halo / kGT;
 }
 
 template <typename TX>

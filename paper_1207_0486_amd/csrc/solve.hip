@@ -402,8 +402,9 @@ public:
     // them waits for the room.  A chunk's end and start cost some 40 us, so one solve
     // by itself takes long ones; where a chunk ends does not change the arithmetic.
     // Solves of 9,801 rows every 2 ms beside one of 1,387,029 rows that runs all the
-    // time: 1.8 ms each (p99 3.0) with turns of 1 ms, 4.0 (6.0) with 2 ms, 0.6 (0.6)
-    // with launches per phase; the large one 9.5, 11.5 and 11.6 solves per second.
+    // time, and two more: 2.2 ms each (p99 4.4) with turns of 1 ms, 4.0 (6.0) with 1.4,
+    // 0.6 (0.6) with launches per phase; the large one 10.9, 11.5 and 11.6 solves per
+    // second.
     int iterations(const GridPlan &p, int most) const
     {
         return alone ? most : std::max(1, std::min(most, (int)(1e3 / std::max(p.cost, 1.0))));

@@ -406,7 +406,7 @@ int hns_operator_assembly(const hns_operator *op);
  *                  rule, dot products summed over 1024 threads instead of
  *                  per-block partials; up to 4096 rows the vectors stay in
  *                  registers and LDS for the whole chunk; FP64 solves of up
- *                  to 2560 rows with at most seven upper diagonals run whole
+ *                  to 2560 rows with exactly seven upper diagonals run whole
  *                  in one launch of 512 threads: statistics, residuals,
  *                  restarts and normalisation too).  The workgroup
  *                  stops by itself at the tolerance, so its chunks take up
@@ -446,9 +446,12 @@ int hns_operator_assembly(const hns_operator *op);
  *                  vectors on chip and the workgroups meeting once per dot
  *                  product: the same recurrence and stopping rule, the dot
  *                  products summed in another order.  -1 (default) where a
- *                  tiling fits (7 upper diagonals; the rows of one tile's
- *                  vectors in LDS: up to about 1.5M rows) and "fuse_dir" is
- *                  -1, 0 never.  Not used while per-kernel timing is enabled.
+ *                  tiling fits and "fuse_dir" is -1, 0 never.  Tilings:
+ *                  exactly 7 upper diagonals, at most 6144 rows in each of
+ *                  256 workgroups (1.57M rows), whose vectors and edges (at
+ *                  most 2048 rows) fit a CU's LDS; tall columns and thick
+ *                  planes have longer edges (60x60x200 and 100x100x100 cells
+ *                  fit no tiling).  Not used while per-kernel timing is enabled.
  *                  Chunks of concurrent solves run side by side where
  *                  their workgroups fit the GPU's CUs together (one each),
  *                  else they take turns of about 1 ms in the order they

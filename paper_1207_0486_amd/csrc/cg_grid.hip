@@ -50,8 +50,9 @@
 // thread until it ends: eight threads solving 41,664 rows each got 192 solves per
 // second that way, 370 with launches per phase.)  A poll is bounded all the same:
 // on running out, the workgroup raises Scalars::lost and leaves, the others run out
-// in turn, and the caller repeats the segment with a launch per phase (x is written
-// by the segment's end only, so nothing is lost but time).
+// in turn, and the caller repeats the segment with a launch per phase: r, p and x are
+// void then, and x is the segment's correction (some forms update it in memory in
+// every iteration), never the caller's x, so nothing is lost but time.
 #include <algorithm>
 #include <cmath>
 

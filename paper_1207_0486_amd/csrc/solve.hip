@@ -1516,8 +1516,9 @@ static hns_status finish_diagonal(hns_operator *op, const HostCSR &A,
 // Auxiliary forms of the step right-hand sides.  The consistent mass shares
 // the pattern and symmetry of A and takes diagonal storage where A's stencil
 // allows it (no column indices: about a third of the CSR bytes on the layered
-// meshes); the divergence forms are not symmetric and the surface mass lives
-// on the surface rows only, so those stay in CSR.
+// meshes); the divergence forms have that pattern without the symmetry and then
+// take two arrays per offset (hns_operator::Bdia), else CSR with their transposes;
+// the surface mass lives on the surface rows only and stays in CSR.
 static hns_status assemble_step_aux(hns_operator *op, const hns_mesh *mesh, const HostCSR &A)
 {
     if (op->kind != HNS_HELMHOLTZ) {

@@ -184,7 +184,7 @@ class Operator:
         st = L.lib().hns_one_launch_read(self._h, int(mode == "mixed"), C.byref(info))
         if st != L.HNS_OK:
             raise HNSError(st, "hns_one_launch_read")
-        return {k: int(getattr(info, k)) for k, _ in info._fields_ if k != "reserved"}
+        return {k: int(getattr(info, k)) for k, _ in info._fields_}
 
     def profile(self, period: int = 1):
         """Time every `period`-th CG iteration with HIP events (0 = off)."""

@@ -96,6 +96,16 @@ def solve_bytes(info, fmt, n, nnz, mode, scaled=False):
             + (info.outer_iterations + 1) * (bytes_residual(fmt, n, nnz) + 8 * 3 * n))
 
 
+def timed_bytes(info, op, fmt, n, nnz, scaled):
+    """Bytes the iterations of an FP64 solve move on the path that ran: chunks in one
+    launch read or write `streamed` values of a row per iteration and keep the rest
+    on chip; else as solve_bytes."""
+    plan = op.one_launch_info("fp64")
+    if plan["chunks"] > 0:
+        return info.iterations * 8 * n * plan["streamed"]
+    return solve_bytes(info, fmt, n, nnz, "fp64", scaled)
+
+
 def make_forcing(m):
     import basin
     L = m.Ly
@@ -1199,6 +1209,9 @@ def main():
     scaled = jacobi_scaled(pois)
     bytes64 = sum(solve_bytes(i, fmt, n, nnz, "fp64") for i in infos64.values())
     moved64 = sum(solve_bytes(i, fmt, n, nnz, "fp64", scaled) for i in infos64.values())
+    timed64 = sum(timed_bytes(i, pois if k == "q" else helm, fmt, n, nnz, scaled)
+                  for k, i in infos64.items())
+    plans64 = {"helm": helm.one_launch_info(), "pois": pois.one_launch_info()}
     csr_equiv = sum(solve_bytes(i, "csr", n, nnz, "fp64") for i in infos64.values())
     gbs64 = bytes64 / (ms64 * 1e-3) / 1e9
     log(f"fp64: {ms64:.1f} ms/step, {gbs64:.0f} GB/s, iters "
@@ -1362,8 +1375,14 @@ def main():
                            if scaled else
                            "operator read + 12 vector passes per Jacobi-PCG iteration")
                         + "). Chunks in one launch keep most of the vectors and part of the "
-                          "operator on chip and move fewer; launch_per_phase is the same step "
-                          "moving them all"),
+                          "operator on chip and move fewer (timed_path); launch_per_phase is the "
+                          "same step moving them all"),
+        "timed_path": {"moved_GBs": round(timed64 / (ms64 * 1e-3) / 1e9, 2),
+                       "one_launch": plans64,
+                       "basis": "bytes the iterations of the timed path itself read and write in "
+                                "memory (chunks in one launch: the values of a row that do not "
+                                "stay on chip) / step time; much of it is served by the caches "
+                                "between iterations"},
         "launch_per_phase": {"ms_per_step": round(prof64["step_ms"], 3),
                              "moved_GBs": round(moved64 / (prof64["step_ms"] * 1e-3) / 1e9, 2),
                              "basis": "one step with kernel timing on, every CG phase a launch"},

@@ -509,7 +509,8 @@ typedef struct {
     int32_t workgroups;       /* of a chunk                                          */
     int32_t rows_per_thread;  /* of the compiled form in use                         */
     int32_t lds_bytes;        /* dynamic LDS of a workgroup                          */
-    int32_t reserved;
+    int32_t streamed;         /* values of a row read or written in memory per
+                                 iteration (matrix, x); the rest stays on chip       */
     int64_t chunks;           /* chunks run to their end                             */
     int64_t missed;           /* chunks whose workgroups gave up waiting             */
     int64_t refused;          /* launches that the device did not take               */

@@ -52,7 +52,7 @@ class hns_solve_info(C.Structure):
 
 class hns_one_launch_info(C.Structure):
     _fields_ = [("workgroups", C.c_int32), ("rows_per_thread", C.c_int32),
-                ("lds_bytes", C.c_int32), ("reserved", C.c_int32),
+                ("lds_bytes", C.c_int32), ("streamed", C.c_int32),
                 ("chunks", C.c_int64), ("missed", C.c_int64), ("refused", C.c_int64)]
 
 

@@ -676,6 +676,7 @@ bool plan_for(const DevMatrix &S, int cus, GridPlan &best)
                 p.H = (int)H;
                 p.instance = i;
                 p.rpt = inst[i].rpt;
+                p.streamed = inst[i].streamed + (inst[i].xreg ? 0 : 2);
                 for (int k = 0; k < m; ++k)
                     p.dl[k] = k < split ? S.off[k] : (int)(pitch + S.off[k] - P);
                 best = p;

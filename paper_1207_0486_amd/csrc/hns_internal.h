@@ -73,6 +73,7 @@ struct GridPlan {
     int dev = 0, room = 0;       // device, and CUs of one of its shader engines
     int G = 0, P = 0, planes = 0, A = 0, S = 0, nS = 0, nch = 0, H = 0, pitch = 0, hcap = 0;
     int instance = 0, rpt = 0;   // the compiled form, and its rows per thread
+    int streamed = 0;            // values of a row read or written in memory per iteration
     int wlds = 0;
     size_t lds = 0;
     double cost = 0;             // estimated us per iteration

@@ -1917,6 +1917,7 @@ hns_status hns_one_launch_read(hns_operator *op, int fp32, hns_one_launch_info *
             info->workgroups = p.G;
             info->rows_per_thread = p.rpt;
             info->lds_bytes = (int32_t)p.lds;
+            info->streamed = p.streamed;
         }
     }
     info->chunks = op->grid_chunks[fp32];

@@ -179,7 +179,8 @@ class Operator:
     def one_launch_info(self, mode: str = "fp64") -> dict:
         """Tiling and counts of the one-launch CG chunks (see "one_launch") in FP64
         ("fp64") or FP32 ("mixed"): workgroups (0: none), rows_per_thread,
-        lds_bytes, chunks, missed, refused."""
+        lds_bytes, streamed (values of a row read or written in memory per
+        iteration), chunks, missed, refused."""
         info = L.hns_one_launch_info()
         st = L.lib().hns_one_launch_read(self._h, int(mode == "mixed"), C.byref(info))
         if st != L.HNS_OK:

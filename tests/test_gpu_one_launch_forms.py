@@ -40,6 +40,10 @@ def _rel(x, y):
     return float((x - y).norm() / y.norm())
 
 
+# values of a row that a form moves through memory per iteration, by rows per
+# thread (FP64): lower diagonals beyond those kept on chip, and x twice
+STREAMED = {1: 0, 2: 0, 4: 0, 6: 2, 8: 5, 12: 11}
+
 # rows per thread of the form that 256 CUs take, in FP64 and FP32
 FORMS = [((30, 28, 7), 1, 1), ((61, 47, 13), 2, 2), ((90, 80, 11), 4, 4), ((180, 190, 21), 6, 8),
          ((240, 189, 17), 8, 8), ((237, 192, 18), 8, 8), ((250, 200, 22), 12, 12)]
@@ -65,6 +69,7 @@ def test_the_expected_form_runs_and_equals_the_launches(dev, grid, rows64, rows3
         assert (op.one_launch_info()["chunks"] > 0) == (one == -1)
     got = op.one_launch_info()
     assert got["rows_per_thread"] == rows64 and got["missed"] == 0
+    assert got["streamed"] == STREAMED[rows64]
     op.close()
     assert _rel(xs[-1], xs[0]) <= 1e-11
     b = _rhs(m, 1, 22, dev)

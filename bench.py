@@ -1004,9 +1004,10 @@ def batched_probe(torch, log, iters=6, k=48):
 def traffic_probe(torch, log, iters=64, q2_iters=16):
     """Short run for hardware-counter passes: a plain 1 GiB device copy (the
     calibration kernel of known size), 64 iterations of the 256x256x20
-    pressure solve (the dominant SpMV kernel), then 16 iterations of the Q2
-    velocity solve on 128x128x10 bricks (the wide diagonal SpMV), then the
-    same 16 iterations on the matrix-free Q2 operator."""
+    pressure solve with a launch per phase (the SpMV kernel) and 64 in one
+    launch, then 16 iterations of the Q2 velocity solve on 128x128x10 bricks
+    (the wide diagonal SpMV), then the same 16 iterations on the matrix-free
+    Q2 operator."""
     import basin
     from paper_1207_0486_amd.hns import Operator
     dev = torch.device("cuda", 0)
@@ -1018,13 +1019,17 @@ def traffic_probe(torch, log, iters=64, q2_iters=16):
     m = wl.mesh()
     pois = Operator(m, wl.nu_h, wl.nu_v, kind="poisson")
     rhs = torch.as_tensor(basin.normal_rhs(m.n, 0, zero_mean=True), device=dev)
+    pois.set_param("one_launch", 0)
+    x, info = pois.solve(rhs, tol=1e-30, max_iter=iters, check=False)
+    pois.set_param("one_launch", -1)
     x, info = pois.solve(rhs, tol=1e-30, max_iter=iters, check=False)
     torch.cuda.synchronize()
     out = {"probe": "traffic", "copy_bytes": 2 * a.numel() * 8, "nodes": m.n, "nnz": pois.nnz,
            "format": pois.format, "iterations": info.iterations,
            "jacobi_scaled": jacobi_scaled(pois),
            "spmv_algorithmic_bytes": bytes_spmv(pois.format, m.n, pois.nnz, 8,
-                                                unit=jacobi_scaled(pois))}
+                                                unit=jacobi_scaled(pois)),
+           "one_launch": pois.one_launch_info()}
     pois.close()
     del a, b
     mq = basin.basin_hex_mesh(128, 128, 10, 2, L=wl.L, seed=wl.seed)

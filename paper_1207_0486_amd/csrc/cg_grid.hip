@@ -41,7 +41,7 @@
 // use otherwise).
 //
 // Progress.  The workgroups wait for each other, so all of a launch must become
-// resident.  One takes a CU (512 threads of 256 registers), and a launch of G is
+// resident.  One takes a CU at most (512 threads, up to 256 registers), and a launch of G is
 // dealt round-robin to the 8 XCDs and the 4 shader engines of each: at most
 // ceil(G / 32) to an engine.  The caller admits launches while the sum of these
 // counts is at most the CUs of an engine (GridTurn in solve.hip), so each finds its

@@ -316,7 +316,8 @@ static bool grid_wanted(const hns_operator *op, const Workspace *w, Prec prec, b
 // Workgroups that missed a meeting will miss the next one too where another
 // process holds their CUs: the operator's next solves (16, twice as many after each
 // further miss) take launches per phase at once instead of waiting out the bound
-// again.  A chunk that runs to its end, or a new setting, ends that.
+// again.  A chunk that runs to its end takes the count back to 16; a new setting
+// ends the rest.
 constexpr int kRestFirst = 16, kRestMost = 1 << 16;
 
 static void grid_rest(hns_operator *op)
@@ -346,6 +347,7 @@ struct GridRoom {
     uint64_t asked = 0, served = 0;
     std::chrono::steady_clock::time_point shared{};   // when two solves last met here
 };
+
 static GridRoom &grid_room(int dev)
 {
     constexpr int kDevices = 64;   // (further devices share the first ones' room)
